@@ -383,7 +383,7 @@ gplhr_status gplhr_gram(int dtype, int64_t n, const void *X, int ldx, int bx, co
             (dtype != 0 && dtype != 1) || !X || !Y || !G)
             throw gplhr::Error(-1, "gplhr_gram: bad arguments");
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
-        const size_t cap = (size_t)1024 * bx * by;
+        const size_t cap = gplhr::gram_part_entries(bx, by);
         int dev = 0;
         GPLHR_HIP_CHECK(hipGetDevice(&dev));
         std::lock_guard<std::mutex> lock(g_gram_mu);
@@ -419,7 +419,7 @@ gplhr_status gplhr_proj_orth(int dtype, int64_t n, void *Z, int ld, int wy, int 
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
         const int wg = wy + w;
         // one allocation: Gram partials | G = [Y X]^H X | R^{-1} | C_Y | counter
-        const size_t cap = (size_t)1024 * wg * w;
+        const size_t cap = gplhr::gram_part_entries(wg, w);
         const size_t nG = (size_t)wg * w, nR = (size_t)w * w, nC = (size_t)std::max(wy, 1) * w;
         double2 *buf = nullptr;
         GPLHR_HIP_CHECK(hipMallocAsync((void **)&buf, sizeof(double2) * (cap + nG + nR + nC + 1), st));
@@ -518,10 +518,8 @@ gplhr_status gplhr_gram_noalloc(int dtype, int64_t n, const void *X, int ldx, in
         if (n < 1 || bx < 1 || by < 1 || bx > 64 || by > 64 || ldx < bx || ldy < by ||
             (dtype != 0 && dtype != 1) || !X || !Y || !G)
             throw gplhr::Error(-1, "gplhr_gram_noalloc: bad arguments");
-        // one block's real partial Gram takes 4 bx by doubles (2 bx by
-        // complex128 entries); the kernel uses as many blocks as fit
-        if ((size_t)2 * bx * by > NOALLOC_SCRATCH_ENTRIES)
-            throw gplhr::Error(-1, "gplhr_gram_noalloc: partial sums exceed the 16 MiB scratch");
+        // one block's partial Gram takes 128 entries per 16x16 tile, at most 64
+        // tiles: the kernel uses as many blocks as fit
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
         double2 *part = scratch_on_current_device();
         if (dtype == 0)

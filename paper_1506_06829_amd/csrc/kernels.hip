@@ -1,7 +1,6 @@
 // HIP kernels (gfx950) for the GPLHR block iteration: CSR sparse-times-block
-// products, FP64-accumulated Gram matrices with a deterministic two-level
-// reduction, row-local block updates staged through LDS, the Cholesky-QR
-// factor, residual norms and the one-time operator setup.
+// products, row-local block updates, the Cholesky-QR factor, residual norms
+// and the one-time operator setup.  (Gram matrices: gram.h.)
 //
 // Layout: every n-by-w block is row-major ("block-row interleaved"): row i of
 // a block is w contiguous complex values, so a sparse-row gather reads whole
@@ -10,61 +9,13 @@
 #include <hipcub/hipcub.hpp>
 
 #include <cmath>
-#include <mutex>
-#include <set>
 #include <cstdint>
 #include <type_traits>
 #include <vector>
 
-#include "internal.h"
+#include "device_math.h"
 
 namespace gplhr {
-
-// ---------------------------------------------------------------------------
-// complex helpers
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-__device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-// acc += a * b
-__device__ __forceinline__ void cfma(double2 &acc, double2 a, double2 b) {
-    acc.x = fma(a.x, b.x, acc.x);
-    acc.x = fma(-a.y, b.y, acc.x);
-    acc.y = fma(a.x, b.y, acc.y);
-    acc.y = fma(a.y, b.x, acc.y);
-}
-__device__ __forceinline__ void cfma(float2 &acc, float2 a, float2 b) {
-    acc.x = fmaf(a.x, b.x, acc.x);
-    acc.x = fmaf(-a.y, b.y, acc.x);
-    acc.y = fmaf(a.x, b.y, acc.y);
-    acc.y = fmaf(a.y, b.x, acc.y);
-}
-// acc += conj(a) * b
-__device__ __forceinline__ void cfma_cj(double2 &acc, double2 a, double2 b) {
-    acc.x = fma(a.x, b.x, acc.x);
-    acc.x = fma(a.y, b.y, acc.x);
-    acc.y = fma(a.x, b.y, acc.y);
-    acc.y = fma(-a.y, b.x, acc.y);
-}
-__device__ __forceinline__ double2 to_d(double2 a) { return a; }
-__device__ __forceinline__ double2 to_d(float2 a) { return make_double2((double)a.x, (double)a.y); }
-template <typename T> __device__ __forceinline__ T from_d(double2 a);
-template <> __device__ __forceinline__ double2 from_d<double2>(double2 a) { return a; }
-template <> __device__ __forceinline__ float2 from_d<float2>(double2 a) {
-    return make_float2((float)a.x, (float)a.y);
-}
-template <typename T> __device__ __forceinline__ T czero();
-template <> __device__ __forceinline__ double2 czero<double2>() { return make_double2(0.0, 0.0); }
-template <> __device__ __forceinline__ float2 czero<float2>() { return make_float2(0.f, 0.f); }
-
-static inline int ceil_div_i(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 // ---------------------------------------------------------------------------
 // CSR sparse matrix times row-major block
@@ -418,453 +369,6 @@ int spmm_plane(hipStream_t st, int64_t n, const int32_t *rp, const int32_t *ci) 
     return 0;
 }
 
-// ---------------------------------------------------------------------------
-// Gram matrices G = X^H diag(yscale) Y in FP64, deterministic
-// The complex product is the real GEMM [Re X, Im X]^T [Re Y, Im Y] over the
-// interleaved real views (n x 2bx and n x 2by), computed with FP64 matrix
-// instructions (16x16x4, FP64 accumulate; complex64 inputs are widened, so
-// every product is exact).  Output tiles (MT x NT of 16x16) are split among
-// the four waves of a block: G groups of N tiles, and ks = 4 / G row splits.
-// Each wave owns at most MTC x NTC tiles and streams its rows with the
-// operands of the next K step (4 rows) in flight while the current one is
-// multiplied: the loads go to raw registers from clamped, always valid
-// addresses, and widening, the B row scale and masking are applied only when
-// an operand is used, so nothing waits on a load before its turn.  Row splits
-// are summed in LDS in a fixed order, and each block writes a real partial
-// Gram of its contiguous row range.
-// Y2 (optional): Y's columns from by1 on come from Y2 (leading dimension
-// ldy2) and only they take the row scale, so two Grams with the same X,
-// X^H Y and X^H diag(s) Y2, are one pass over X.
-template <typename T>
-struct GramMArgs {
-    int64_t n;
-    const T *X;
-    int ldx;
-    int bx;
-    const T *Y;
-    int ldy;
-    int by;
-    const T *yscale;
-    double *part;
-    int nblk;
-    int64_t rows_per_blk;
-    int MT, NT, G, ks, NTg;
-    const T *Y2;
-    int ldy2;
-    int by1;
-};
-
-typedef double d4v __attribute__((ext_vector_type(4)));
-typedef float f4v __attribute__((ext_vector_type(4)));
-
-template <typename T> struct RealOf;
-template <> struct RealOf<double2> { using R = double; };
-template <> struct RealOf<float2> { using R = float; };
-
-constexpr int GM_PF = 4;   // K steps in flight per wave
-
-// OCC: waves per SIMD the register allocation must leave room for (1: the
-// compiler's choice; 2: at most 256 VGPRs + AGPRs per lane).
-template <typename T, int MTC, int NTC, int PF = GM_PF, int OCC = 1>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC, 8)))
-void gram_mfma_kernel(GramMArgs<T> a) {
-    using R = typename RealOf<T>::R;
-    using OpR = double;
-    __shared__ double red[2 * MTC * NTC * 256];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int g = wave % a.G, h = wave / a.G;
-    const int li = lane & 15, lk = lane >> 4;
-    const int nbx = 2 * a.bx, nby = 2 * a.by;
-    const int nt0 = g * a.NTg;
-    // a wave whose column group lies past the Gram's last N tile has nothing to do
-    const bool active = h < a.ks && nt0 < a.NT;
-    d4v acc[MTC][NTC];
-#pragma unroll
-    for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-        for (int t = 0; t < NTC; ++t) acc[mt][t] = d4v{0.0, 0.0, 0.0, 0.0};
-    const int64_t rb = (int64_t)blockIdx.x * a.rows_per_blk;
-    const int64_t re = min(a.n, rb + a.rows_per_blk);
-    const int64_t step = 4LL * a.ks;
-    const int64_t r = rb + 4 * h + lk;
-    const int64_t span = re - rb - 4 * h;
-    const int nst = span > 0 ? (int)((span + step - 1) / step) : 0;
-    R xa[PF][MTC], yra[PF][NTC], yia[PF][NTC];
-    double scr[PF], sci[PF];
-    // raw operands of the K step at `row` (row 0, always valid, past the
-    // block's range; those operands are masked at use)
-    auto load = [&](int p, int64_t row) {
-        const int64_t rr = row < re ? row : 0;
-        const R *xrow = reinterpret_cast<const R *>(a.X + rr * a.ldx);
-#pragma unroll
-        for (int mt = 0; mt < MTC; ++mt) {
-            const int i = mt * 16 + li;
-            xa[p][mt] = xrow[i < nbx ? i : 0];
-        }
-        if (a.yscale) {
-            const double2 sc = to_d(a.yscale[rr]);
-            scr[p] = sc.x;
-            sci[p] = sc.y;
-        }
-#pragma unroll
-        for (int t = 0; t < NTC; ++t) {
-            // the complex entry holding real column j
-            const int j = (nt0 + t) * 16 + li;
-            const int jc = (j < nby ? j : 0) >> 1;
-            const T *yp = (a.Y2 && jc >= a.by1) ? a.Y2 + rr * a.ldy2 + (jc - a.by1) : a.Y + rr * a.ldy + jc;
-            const T yc = *yp;
-            yra[p][t] = yc.x;
-            yia[p][t] = yc.y;
-        }
-    };
-    if (active) {
-#pragma unroll
-        for (int p = 0; p < PF; ++p) load(p, r + (int64_t)p * step);
-        for (int j = 0; j < nst; j += PF) {
-#pragma unroll
-            for (int p = 0; p < PF; ++p) {
-                const bool okp = (r + (int64_t)(j + p) * step) < re;
-                OpR xv[MTC], yv[NTC];
-#pragma unroll
-                for (int mt = 0; mt < MTC; ++mt) {
-                    const int i = mt * 16 + li;
-                    xv[mt] = (okp && i < nbx) ? (OpR)xa[p][mt] : (OpR)0;
-                }
-#pragma unroll
-                for (int t = 0; t < NTC; ++t) {
-                    const int jr = (nt0 + t) * 16 + li;
-                    double v = 0.0;
-                    if (okp && jr < nby) {
-                        const double yr = yra[p][t], yi = yia[p][t];
-                        // (sc * y), the real (jr even) or imaginary part
-                        const bool sc = a.yscale && (!a.Y2 || (jr >> 1) >= a.by1);
-                        if (sc)
-                            v = (jr & 1) ? (scr[p] * yi + sci[p] * yr) : (scr[p] * yr - sci[p] * yi);
-                        else
-                            v = (jr & 1) ? yi : yr;
-                    }
-                    yv[t] = (OpR)v;
-                }
-                // every tile of the wave, without per-tile branches: the
-                // operands of tiles past the Gram's edge are zero, and
-                // branches around the MFMAs would split them into separate
-                // basic blocks (64 x 64 at 4096000 rows: 2783 -> 2436 us)
-#pragma unroll
-                for (int mt = 0; mt < MTC; ++mt) {
-#pragma unroll
-                    for (int t = 0; t < NTC; ++t)
-                        acc[mt][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[mt], yv[t], acc[mt][t], 0, 0, 0);
-                }
-                load(p, r + (int64_t)(j + p + PF) * step);
-            }
-        }
-    }
-    // D(i, j) of a 16x16 tile on gfx950 (FP64 16x16x4): register v of lane l
-    // holds j = l % 16 and i = 4 v + l / 16
-    auto store = [&](int mt, int nt, const d4v &d) {
-        const int jj = nt * 16 + li;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int i = mt * 16 + 4 * v + lk;
-            // block-contiguous partials: this block's nbx-by-nby real Gram
-            if (i < nbx && jj < nby)
-                a.part[(int64_t)blockIdx.x * nbx * nby + i + (int64_t)jj * nbx] = d[v];
-        }
-    };
-    if (a.ks == 1) {
-        if (active) {
-#pragma unroll
-            for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-                for (int t = 0; t < NTC; ++t)
-                    if (mt < a.MT && t < a.NTg && nt0 + t < a.NT) store(mt, nt0 + t, acc[mt][t]);
-        }
-        return;
-    }
-    // ks > 1 (then G <= 2): the row splits are summed in LDS in the order h
-    for (int hh = 0; hh < a.ks; ++hh) {
-        if (h == hh) {
-#pragma unroll
-            for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-                for (int t = 0; t < NTC; ++t) {
-                    if (mt < a.MT && t < a.NTg) {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            double &dst = red[((g * MTC + mt) * NTC + t) * 256 + lane * 4 + v];
-                            dst = (hh == 0) ? acc[mt][t][v] : dst + acc[mt][t][v];
-                        }
-                    }
-                }
-        }
-        __syncthreads();
-    }
-    if (h == 0) {
-#pragma unroll
-        for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-            for (int t = 0; t < NTC; ++t)
-                if (mt < a.MT && t < a.NTg && nt0 + t < a.NT) {
-                    d4v d;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) d[v] = red[((g * MTC + mt) * NTC + t) * 256 + lane * 4 + v];
-                    store(mt, nt0 + t, d);
-                }
-    }
-}
-
-// LDS-staged variant for the wide tall Grams (X up to 8 M tiles, Y more
-// than 2 N tiles, FP64 MFMA): the block walks its rows in chunks of RCH; each
-// chunk's X and Y rows (and the row scale) are read with coalesced loads
-// into registers while the previous chunk is multiplied, then written to the
-// other of two LDS buffers, one barrier per chunk.  Operands come from LDS,
-// zero-padded to whole tiles, so the MFMA loop needs no masks or per-tile
-// branches.  The four wavefronts form GM x GN tile groups (MTg x NTg tiles
-// each) times KS row splits; partial sums as in gram_mfma_kernel.  64 x 64 at
-// 4096000 rows: complex64 2436 -> 2304 us, with a row scale 2817 -> 2475 us;
-// complex128 2584 -> 2373 us.
-template <typename T>
-struct GramLArgs {
-    int64_t n;
-    const T *X; int ldx; int bx;
-    const T *Y; int ldy; int by;
-    const T *yscale;
-    double *part;
-    int nblk;
-    int64_t rows_per_blk;
-    int MT, NT, GM, GN, KS, MTg, NTg;
-};
-
-template <typename T, int MTC, int NTC, int XTC, int YTC, int RCH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8)))
-void gram_lds_kernel(GramLArgs<T> a) {
-    constexpr int WAVES = 4;
-    using R = typename RealOf<T>::R;
-    using OpR = double;
-    constexpr int NTH = WAVES * 64;
-    constexpr int PADR = 16;
-    constexpr int XS = XTC * 16 + PADR, YS = YTC * 16 + PADR;    // reals per LDS row
-    constexpr size_t STAGE = (size_t)2 * RCH * (XS + YS) * sizeof(R) + 2 * RCH * sizeof(double2);
-    constexpr size_t RED = (size_t)(WAVES / 2) * MTC * NTC * 256 * sizeof(double);   // KS > 1: at most WAVES / 2 tile groups
-    constexpr size_t LDSB = STAGE > RED ? STAGE : RED;
-    __shared__ __attribute__((aligned(16))) unsigned char lds[LDSB];
-    R *Xs = reinterpret_cast<R *>(lds);                  // [2][RCH][XS]
-    R *Ys = Xs + 2 * RCH * XS;                           // [2][RCH][YS]
-    double2 *Ss = reinterpret_cast<double2 *>(Ys + 2 * RCH * YS);   // [2][RCH]
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int ngrp = a.GM * a.GN;
-    const int kh = wave / ngrp, grp = wave - kh * ngrp;
-    const int gm = grp / a.GN, gn = grp - gm * a.GN;
-    const int li = lane & 15, lk = lane >> 4;
-    const int nbx = 2 * a.bx, nby = 2 * a.by;
-    const int mt0 = gm * a.MTg, nt0 = gn * a.NTg;
-    const int xw = a.MT * 16, yw = a.NT * 16;             // staged real widths
-    for (int e = tid; e < 2 * RCH * (xw - nbx); e += NTH) {
-        const int r = e / (xw - nbx), c = nbx + e % (xw - nbx);
-        Xs[r * XS + c] = (R)0;
-    }
-    for (int e = tid; e < 2 * RCH * (yw - nby); e += NTH) {
-        const int r = e / (yw - nby), c = nby + e % (yw - nby);
-        Ys[r * YS + c] = (R)0;
-    }
-    d4v acc[MTC][NTC];
-#pragma unroll
-    for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-        for (int t = 0; t < NTC; ++t) acc[mt][t] = d4v{0.0, 0.0, 0.0, 0.0};
-    const int64_t rb = (int64_t)blockIdx.x * a.rows_per_blk;
-    const int64_t re = min(a.n, rb + a.rows_per_blk);
-    const int nch = re > rb ? (int)((re - rb + RCH - 1) / RCH) : 0;
-    constexpr int NLX = (RCH * XTC * 8 + NTH - 1) / NTH, NLY = (RCH * YTC * 8 + NTH - 1) / NTH;
-    T sx[NLX], sy[NLY];
-    double2 ssc = make_double2(0.0, 0.0);
-    const bool scaled = a.yscale != nullptr;
-    auto gload = [&](int ch) {
-        const int64_t r0 = rb + (int64_t)ch * RCH;
-#pragma unroll
-        for (int i = 0; i < NLX; ++i) {
-            const int e = tid + NTH * i;
-            const int r = e / a.bx, c = e - r * a.bx;
-            const int64_t row = r0 + r;
-            sx[i] = (r < RCH && row < re) ? a.X[row * a.ldx + c] : czero<T>();
-        }
-#pragma unroll
-        for (int i = 0; i < NLY; ++i) {
-            const int e = tid + NTH * i;
-            const int r = e / a.by, c = e - r * a.by;
-            const int64_t row = r0 + r;
-            sy[i] = (r < RCH && row < re) ? a.Y[row * a.ldy + c] : czero<T>();
-        }
-        if (scaled && tid < RCH) {
-            const int64_t row = r0 + tid;
-            ssc = row < re ? to_d(a.yscale[row]) : make_double2(0.0, 0.0);
-        }
-    };
-    auto lstore = [&](int buf) {
-        R *xb = Xs + buf * RCH * XS;
-        R *yb = Ys + buf * RCH * YS;
-#pragma unroll
-        for (int i = 0; i < NLX; ++i) {
-            const int e = tid + NTH * i;
-            const int r = e / a.bx, c = e - r * a.bx;
-            if (r < RCH) *reinterpret_cast<T *>(xb + r * XS + 2 * c) = sx[i];
-        }
-#pragma unroll
-        for (int i = 0; i < NLY; ++i) {
-            const int e = tid + NTH * i;
-            const int r = e / a.by, c = e - r * a.by;
-            if (r < RCH) *reinterpret_cast<T *>(yb + r * YS + 2 * c) = sy[i];
-        }
-        if (scaled && tid < RCH) Ss[buf * RCH + tid] = ssc;
-    };
-    if (nch > 0) {
-        gload(0);
-        lstore(0);
-    }
-    __syncthreads();
-    const bool active = kh < a.KS;
-    constexpr int MP = 1, MTP = MTC;
-    for (int ch = 0; ch < nch; ++ch) {
-        const int buf = ch & 1;
-        if (ch + 1 < nch) gload(ch + 1);
-        const R *xb = Xs + buf * RCH * XS;
-        const R *yb = Ys + buf * RCH * YS;
-        const double2 *sb = Ss + buf * RCH;
-        if (active) {
-#pragma unroll
-            for (int pass = 0; pass < MP; ++pass) {
-    #pragma unroll 4
-            for (int kk = kh; kk < RCH / 4; kk += a.KS) {
-                    const int rr = 4 * kk + lk;
-                    OpR xv[MTP], yv[NTC];
-#pragma unroll
-                    for (int m = 0; m < MTP; ++m)
-                        xv[m] = (OpR)xb[rr * XS + (mt0 + pass * MTP + m) * 16 + li];
-                    if (scaled) {
-                        const double2 sc = sb[rr];
-#pragma unroll
-                        for (int t = 0; t < NTC; ++t) {
-                            const int jr = (nt0 + t) * 16 + li;
-                            const int jc = jr & ~1;
-                            const double yr = (double)yb[rr * YS + jc], yi = (double)yb[rr * YS + jc + 1];
-                            yv[t] = (OpR)((jr & 1) ? (sc.x * yi + sc.y * yr) : (sc.x * yr - sc.y * yi));
-                        }
-                    } else {
-#pragma unroll
-                        for (int t = 0; t < NTC; ++t) yv[t] = (OpR)yb[rr * YS + (nt0 + t) * 16 + li];
-                    }
-#pragma unroll
-                    for (int m = 0; m < MTP; ++m) {
-                        const int mt = pass * MTP + m;
-#pragma unroll
-                        for (int t = 0; t < NTC; ++t) {
-                            acc[mt][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                                xv[m], yv[t], acc[mt][t], 0, 0, 0);
-                        }
-                    }
-                }
-            }
-        }
-        if (ch + 1 < nch) lstore(buf ^ 1);
-        __syncthreads();
-    }
-    auto store = [&](int mt, int nt, const d4v &d) {
-        const int jj = nt * 16 + li;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int i = mt * 16 + 4 * v + lk;
-            if (i < nbx && jj < nby)
-                a.part[(int64_t)blockIdx.x * nbx * nby + i + (int64_t)jj * nbx] = d[v];
-        }
-    };
-    auto owned = [&](int mt, int t) { return mt < a.MTg && mt0 + mt < a.MT && t < a.NTg && nt0 + t < a.NT; };
-    if (a.KS == 1) {
-        if (active) {
-#pragma unroll
-            for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-                for (int t = 0; t < NTC; ++t)
-                    if (owned(mt, t)) store(mt0 + mt, nt0 + t, acc[mt][t]);
-        }
-        return;
-    }
-    // KS > 1: row splits summed in LDS in the order kh
-    double *red = reinterpret_cast<double *>(lds);
-    for (int hh = 0; hh < a.KS; ++hh) {
-        if (kh == hh) {
-#pragma unroll
-            for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-                for (int t = 0; t < NTC; ++t)
-                    if (owned(mt, t)) {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            double &dst = red[((grp * MTC + mt) * NTC + t) * 256 + lane * 4 + v];
-                            dst = (hh == 0) ? acc[mt][t][v] : dst + acc[mt][t][v];
-                        }
-                    }
-        }
-        __syncthreads();
-    }
-    if (kh == 0) {
-#pragma unroll
-        for (int mt = 0; mt < MTC; ++mt)
-#pragma unroll
-            for (int t = 0; t < NTC; ++t)
-                if (owned(mt, t)) {
-                    d4v d;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) d[v] = red[((grp * MTC + mt) * NTC + t) * 256 + lane * 4 + v];
-                    store(mt0 + mt, nt0 + t, d);
-                }
-    }
-}
-
-// complex G(p, q) = (rr + ii) + i (ri - ir) from the real partial Grams of
-// nblk blocks, stored block after block (part[blk E + i + j nbx], E = nbx nby,
-// nbx = 2 bx, nby = 2 by).  A workgroup takes 8 consecutive p of one column q:
-// the 32 reals of rows 2 p0 .. 2 p0 + 15 in real columns 2q and 2q + 1, i.e.
-// two contiguous 128-byte segments per block.  Thread t sums value t % 32 over
-// the blocks t / 32, t / 32 + 8, ... in that order, and the 8 partial sums
-// are added in LDS in a fixed order, so the result is reproducible bit for bit.
-__global__ __launch_bounds__(256) void reduce_real_partials_kernel(const double *part, int nblk,
-                                                                  int bx, int by, double2 *out,
-                                                                  int ldo, int ctrans) {
-    __shared__ double sh[8][32];
-    const int nbx = 2 * bx;
-    const int64_t E = (int64_t)nbx * 2 * by;
-    const int ptiles = (bx + 7) / 8;
-    const int p0 = (blockIdx.x % ptiles) * 8, q = blockIdx.x / ptiles;
-    const int t = threadIdx.x, v = t & 31, g = t >> 5;
-    const int i = 2 * p0 + (v & 15);   // real row
-    const int jc = 2 * q + (v >> 4);   // real column
-    double acc = 0.0;
-    if (i < nbx) {
-        // eight loads in flight per thread; the additions keep their order
-        const double *src = part + i + (int64_t)jc * nbx;
-#pragma unroll 8
-        for (int blk = g; blk < nblk; blk += 8) acc += src[blk * E];
-    }
-    sh[g][v] = acc;
-    __syncthreads();
-    if (t < 32) {
-        double sum = 0.0;
-#pragma unroll
-        for (int gg = 0; gg < 8; ++gg) sum += sh[gg][t];
-        sh[0][t] = sum;
-    }
-    __syncthreads();
-    if (t < 8 && p0 + t < bx) {
-        // real column 2q: rows 2p (rr) and 2p + 1 (ir); column 2q + 1: ri, ii
-        const double rr = sh[0][2 * t], ir = sh[0][2 * t + 1];
-        const double ri = sh[0][16 + 2 * t], ii = sh[0][16 + 2 * t + 1];
-        // ctrans: the partials are of the swapped product, G(q, p) = conj of this
-        if (ctrans) out[q + (int64_t)(p0 + t) * ldo] = make_double2(rr + ii, ir - ri);
-        else out[p0 + t + (int64_t)q * ldo] = make_double2(rr + ii, ri - ir);
-    }
-}
-
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const double2 *part, int nblk,
                                                               int bx, double2 *out, int ldo) {
     __shared__ double2 sh[256];
@@ -890,191 +394,6 @@ void launch_reduce_partials(hipStream_t st, const double2 *part, int nblk, int b
                        out, ldo);
     GPLHR_HIP_CHECK(hipGetLastError());
 }
-
-template <typename T, int MTC, int NTC, int PF = GM_PF, int OCC = 1>
-static void gram_launch_variant(hipStream_t st, GramMArgs<T> a, size_t part_cap, double2 *out,
-                                int ldo, int nblk_want, int ctrans = 0) {
-    a.G = (a.NT + NTC - 1) / NTC;
-    if (a.G == 3) a.G = 4;
-    if (a.MT > MTC || a.G > 4) throw Error(-1, "gram: no tile layout for this shape");
-    a.NTg = (a.NT + a.G - 1) / a.G;
-    a.ks = 4 / a.G;
-    const int64_t step = 4LL * a.ks;
-    // at least a few K steps per wave, and the partials within the scratch
-    const int64_t per_blk = (int64_t)4 * a.bx * a.by;   // doubles
-    int64_t nblk = std::min<int64_t>(nblk_want, std::max<int64_t>(1, a.n / (step * 8)));
-    nblk = std::min<int64_t>(nblk, (int64_t)(2 * part_cap) / per_blk);
-    if (nblk < 1) throw Error(-1, "gram: partial buffer too small");
-    a.rows_per_blk = ((a.n + nblk - 1) / nblk + step - 1) / step * step;
-    // no block starts past the last row
-    a.nblk = (int)((a.n + a.rows_per_blk - 1) / a.rows_per_blk);
-    hipLaunchKernelGGL((gram_mfma_kernel<T, MTC, NTC, PF, OCC>), dim3(a.nblk), dim3(256), 0, st, a);
-    GPLHR_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(reduce_real_partials_kernel, dim3(((a.bx + 7) / 8) * a.by), dim3(256), 0, st,
-                       a.part, a.nblk, a.bx, a.by, out, ldo, ctrans);
-    GPLHR_HIP_CHECK(hipGetLastError());
-}
-
-template <typename T, int MTC, int NTC>
-static void gram_launch_lds_tiles(hipStream_t st, const GramMArgs<T> &m, size_t part_cap, double2 *out,
-                                  int ldo, int ctrans) {
-    constexpr int XTC = 8, YTC = 8, RCH = 16;
-    GramLArgs<T> a{};
-    a.n = m.n; a.X = m.X; a.ldx = m.ldx; a.bx = m.bx; a.Y = m.Y; a.ldy = m.ldy; a.by = m.by;
-    a.yscale = m.yscale; a.part = m.part; a.MT = m.MT; a.NT = m.NT;
-    a.GM = (a.MT + MTC - 1) / MTC;
-    a.GN = (a.NT + NTC - 1) / NTC;
-    if (a.GM * a.GN > 4 || a.MT > XTC || a.NT > YTC) throw Error(-1, "gram: no tile layout for this shape");
-    a.MTg = (a.MT + a.GM - 1) / a.GM;
-    a.NTg = (a.NT + a.GN - 1) / a.GN;
-    a.KS = 4 / (a.GM * a.GN);
-    const int64_t per_blk = (int64_t)4 * a.bx * a.by;   // doubles
-    int64_t nblk = std::min<int64_t>(512, std::max<int64_t>(1, a.n / (2 * RCH)));
-    nblk = std::min<int64_t>(nblk, (int64_t)(2 * part_cap) / per_blk);
-    if (nblk < 1) throw Error(-1, "gram: partial buffer too small");
-    a.rows_per_blk = ((a.n + nblk - 1) / nblk + RCH - 1) / RCH * RCH;
-    a.nblk = (int)((a.n + a.rows_per_blk - 1) / a.rows_per_blk);
-    hipLaunchKernelGGL((gram_lds_kernel<T, MTC, NTC, XTC, YTC, RCH>), dim3(a.nblk), dim3(256), 0, st, a);
-    GPLHR_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(reduce_real_partials_kernel, dim3(((a.bx + 7) / 8) * a.by), dim3(256), 0, st,
-                       a.part, a.nblk, a.bx, a.by, out, ldo, ctrans);
-    GPLHR_HIP_CHECK(hipGetLastError());
-}
-
-// Tile sets of the LDS-staged Gram: 8 x 2 tiles per wave (four column groups)
-// for Y of 7 or 8 N tiles; for 5 or 6 N tiles, where a fourth column group of
-// 2 would be idle, 4 x 3 tiles (two row groups times two column groups).  At
-// 4096000 rows, 64 x 48: complex64 2299 -> 1830 us, complex128 2324 -> 1965 us.
-template <typename T>
-static void gram_launch_lds(hipStream_t st, const GramMArgs<T> &m, size_t part_cap, double2 *out, int ldo,
-                            int ctrans = 0) {
-    if (m.NT <= 6) gram_launch_lds_tiles<T, 4, 3>(st, m, part_cap, out, ldo, ctrans);
-    else gram_launch_lds_tiles<T, 8, 2>(st, m, part_cap, out, ldo, ctrans);
-}
-
-template <typename T>
-static void launch_gram_impl(hipStream_t st, int64_t n, const T *X, int ldx, int bx, const T *Y,
-                             int ldy, int by, const T *yscale, double2 *part, size_t part_cap,
-                             double2 *out, int ldo, const T *Y2 = nullptr, int ldy2 = 0, int by1 = 0) {
-    if (bx < 1 || by < 1 || bx > 64 || by > 64) throw Error(-1, "gram: width out of range");
-    if (n <= 0) throw Error(-1, "gram: empty block");
-    const bool two = Y2 != nullptr;
-    // X at most 16 columns against a wider Y (no row scale): the product is
-    // formed as Y^H X, whose narrow side is the one the tile sets are built
-    // for, and written conjugate-transposed (16 x 48 at 4096000 rows: the
-    // direct form runs a third of its M tiles on zeros)
-    if (!two && !yscale && bx <= 16 && by > 16 && n >= ((int64_t)1 << 20)) {
-        GramMArgs<T> a{};
-        a.n = n; a.X = Y; a.ldx = ldy; a.bx = by; a.Y = X; a.ldy = ldx; a.by = bx;
-        a.part = reinterpret_cast<double *>(part);
-        a.MT = (2 * by + 15) / 16;
-        a.NT = (2 * bx + 15) / 16;
-        if (a.MT == 3) gram_launch_variant<T, 3, 2, GM_PF, 1>(st, a, part_cap, out, ldo, 256, 1);
-        else if (a.MT == 4) gram_launch_variant<T, 4, 2, GM_PF, 1>(st, a, part_cap, out, ldo, 256, 1);
-        else if (a.MT == 5) gram_launch_variant<T, 5, 2, 2, 2>(st, a, part_cap, out, ldo, 512, 1);
-        else if (a.MT == 6) gram_launch_variant<T, 6, 2, 2, 2>(st, a, part_cap, out, ldo, 512, 1);
-        else gram_launch_variant<T, 8, 2, 2, 2>(st, a, part_cap, out, ldo, 512, 1);
-        return;
-    }
-    GramMArgs<T> a{};
-    a.n = n; a.X = X; a.ldx = ldx; a.bx = bx; a.Y = Y; a.ldy = ldy; a.by = by;
-    a.yscale = yscale;
-    a.Y2 = Y2; a.ldy2 = ldy2; a.by1 = by1;
-    a.part = reinterpret_cast<double *>(part);
-    a.MT = (2 * bx + 15) / 16;
-    a.NT = (2 * by + 15) / 16;
-    // tile layout per wave by the number of M tiles; blocks and K steps in
-    // flight measured on n = 262144 and 4096000: narrow X (at most 2 M tiles)
-    // takes 512 blocks, wider shapes 256 (one block per CU at their VGPR use)
-    const int nb = (a.MT <= 2) ? 512 : 256;
-    // Tall blocks (from 2^20 rows): the tile sets that hold one wave per SIMD
-    // at their own register use are built for two (two K steps in flight
-    // instead of four) and launched as 512 blocks, two per CU.  At 4096000
-    // rows: 64 x 64 3326 -> 3030 us, 48 x 48 2021 -> 1811 us, 32 x 32
-    // 1043 -> 984 us, 64 x 16 1129 -> 1055 us; at 262144 rows 48 x 48 went
-    // the other way (180 -> 200 us), hence the row threshold.
-    const bool tall = a.n >= ((int64_t)1 << 20);
-    if (a.NT <= 2) {
-        // Y at most 16 columns wide (the projections against the trial or
-        // test basis): MT x 2 tiles per wave, rows split over the 4 waves; a
-        // wider compiled tile set would only cost registers (4096000 rows:
-        // 40 x 10 924 -> 633 us, 30 x 10 686 -> 526 us)
-        if (a.MT <= 2) gram_launch_variant<T, 2, 2, GM_PF, 1>(st, a, part_cap, out, ldo, nb);
-        else if (a.MT == 3) gram_launch_variant<T, 3, 2, GM_PF, 1>(st, a, part_cap, out, ldo, nb);
-        else if (a.MT == 4) {
-            // built for two waves per SIMD: 32 x 16 at 4096000 rows complex64
-            // 475 -> 373 us (1024 blocks), complex128 535 -> 529 us (512);
-            // 262144 rows 44 -> 39 and 46 -> 42 us (512)
-            const int nb4 = (tall && sizeof(T) == 8) ? 1024 : 512;
-            gram_launch_variant<T, 4, 2, 2, 2>(st, a, part_cap, out, ldo, nb4);
-        } else if (a.MT == 5) {
-            if (tall) gram_launch_variant<T, 5, 2, 2, 2>(st, a, part_cap, out, ldo, 512);
-            else gram_launch_variant<T, 5, 2, GM_PF, 1>(st, a, part_cap, out, ldo, nb);
-        } else if (a.MT == 6) {
-            if (tall) gram_launch_variant<T, 6, 2, 2, 2>(st, a, part_cap, out, ldo, 512);
-            else gram_launch_variant<T, 6, 2, GM_PF, 1>(st, a, part_cap, out, ldo, nb);
-        } else {
-            if (tall) gram_launch_variant<T, 8, 2, 2, 2>(st, a, part_cap, out, ldo, 512);
-            else gram_launch_variant<T, 8, 2, GM_PF, 1>(st, a, part_cap, out, ldo, nb);
-        }
-    } else if (two && a.MT <= 2 && a.NT <= 4) {
-        // [V^H C V, V^H B V] of a 16-wide block (4096000 rows): complex64
-        // 2 x 4 tiles per wave (590 us, the two Grams apart 707 us), complex128
-        // 2 x 2 with two column groups (638 against 733 us); the 3 x 3 set
-        // would run a third of its tiles on zeros (1085 / 1198 us)
-        if constexpr (sizeof(T) == 8) gram_launch_variant<T, 2, 4, GM_PF, 1>(st, a, part_cap, out, ldo, 512);
-        else gram_launch_variant<T, 2, 2, GM_PF, 1>(st, a, part_cap, out, ldo, 512);
-    } else if (a.MT <= 3)
-        gram_launch_variant<T, 3, 3, GM_PF, 1>(st, a, part_cap, out, ldo, nb);
-    else if (a.MT == 4) {
-        if (tall) gram_launch_variant<T, 4, 4, 2, 2>(st, a, part_cap, out, ldo, 512);
-        else gram_launch_variant<T, 4, 4, GM_PF, 1>(st, a, part_cap, out, ldo, nb);
-    } else if (a.MT == 5) {
-        // 40-column X (a 10-wide block's pencil and test-basis Grams).  Below
-        // 2^20 rows, 512 blocks: 5 N tiles as two column groups of 3 built for
-        // two waves per SIMD, 3 or 4 N tiles as groups of 2 with four K steps
-        // in flight (262144 rows: 40 x 40 complex128 137 -> 115 us, complex64
-        // 132 -> 105 us; 40 x 30 complex64 126 -> 89 us).  Tall blocks keep
-        // the one-group layout with two K steps in flight (more would spill).
-        if (tall) gram_launch_variant<T, 5, 5, 2, 1>(st, a, part_cap, out, ldo, nb);
-        else if (a.NT == 5) gram_launch_variant<T, 5, 3, 2, 2>(st, a, part_cap, out, ldo, 512);
-        else gram_launch_variant<T, 5, 2, GM_PF, 1>(st, a, part_cap, out, ldo, 512);
-    }
-    else if (a.MT == 6) {
-        if (tall) gram_launch_variant<T, 6, 3, 2, 2>(st, a, part_cap, out, ldo, 512);
-        else gram_launch_variant<T, 6, 3, GM_PF, 1>(st, a, part_cap, out, ldo, nb);
-    } else {
-        // (Y wider than 32 columns: at 64 x 32 the register-streaming kernel
-        // measured faster, 1219 against 1320 us for complex64)
-        if (tall && a.NT > 4 && !two) gram_launch_lds<T>(st, a, part_cap, out, ldo);
-        else if (tall) gram_launch_variant<T, 8, 2, 2, 2>(st, a, part_cap, out, ldo, 512);
-        else gram_launch_variant<T, 8, 2, GM_PF, 1>(st, a, part_cap, out, ldo, nb);
-    }
-}
-template <typename T>
-void launch_gram(hipStream_t st, int64_t n, const T *X, int ldx, int bx, const T *Y, int ldy,
-                 int by, const T *yscale, double2 *part, size_t part_cap, double2 *out, int ldo) {
-    launch_gram_impl<T>(st, n, X, ldx, bx, Y, ldy, by, yscale, part, part_cap, out, ldo);
-}
-template <typename T>
-void launch_gram2(hipStream_t st, int64_t n, const T *X, int ldx, int bx, const T *Y1, int ldy1,
-                  int by1, const T *Y2, int ldy2, int by2, const T *yscale2, double2 *part,
-                  size_t part_cap, double2 *out, int ldo) {
-    if (!Y1 || !Y2 || by1 < 1 || by2 < 1) throw Error(-1, "gram: two-part Y needs both parts");
-    launch_gram_impl<T>(st, n, X, ldx, bx, Y1, ldy1, by1 + by2, yscale2, part, part_cap, out, ldo,
-                        Y2, ldy2, by1);
-}
-template void launch_gram2<double2>(hipStream_t, int64_t, const double2 *, int, int, const double2 *,
-                                    int, int, const double2 *, int, int, const double2 *, double2 *,
-                                    size_t, double2 *, int);
-template void launch_gram2<float2>(hipStream_t, int64_t, const float2 *, int, int, const float2 *, int,
-                                   int, const float2 *, int, int, const float2 *, double2 *, size_t,
-                                   double2 *, int);
-template void launch_gram<double2>(hipStream_t, int64_t, const double2 *, int, int,
-                                   const double2 *, int, int, const double2 *, double2 *, size_t,
-                                   double2 *, int);
-template void launch_gram<float2>(hipStream_t, int64_t, const float2 *, int, int, const float2 *,
-                                  int, int, const float2 *, double2 *, size_t, double2 *, int);
 
 // ---------------------------------------------------------------------------
 // row-local block update
@@ -1423,25 +742,6 @@ static void launch_update_mfma(hipStream_t st, const UpdArgs<T> &a, int kpad) {
     hipLaunchKernelGGL((update_mfma_kernel<T, MT, NT, 2>), dim3(grid), dim3(256), shmem, st, a, kpad);
 }
 
-// Launch with dynamic LDS, raising the kernel's limit above the 64 KiB
-// default when it needs more (gfx950: 160 KiB per workgroup), once per
-// kernel and device.
-static void allow_large_lds(const void *kernel) {
-    static std::mutex mu;
-    static std::set<std::pair<int, const void *>> done;
-    int dev = 0;
-    GPLHR_HIP_CHECK(hipGetDevice(&dev));
-    std::lock_guard<std::mutex> lock(mu);
-    if (done.count({dev, kernel})) return;
-    GPLHR_HIP_CHECK(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-    done.insert({dev, kernel});
-}
-template <typename K, typename... Args>
-static void launch_lds_kernel(K kernel, int grid, size_t shmem, hipStream_t st, Args... args) {
-    if (shmem > 64 * 1024) allow_large_lds(reinterpret_cast<const void *>(kernel));
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), shmem, st, args...);
-}
-
 // Pipelined MFMA kernel for the streaming shapes (inputs at most 64 complex
 // columns, at most one row-scale vector).  A wavefront owns row groups of 16
 // MT rows, as in update_mfma_kernel, but loads all S slabs of its next row
@@ -1697,15 +997,15 @@ static void launch_update_pipe(hipStream_t st, const UpdArgs<T> &a, int kpad) {
         // upper triangular R^{-1} and 16 more): 15 of the 36 products of the
         // triangular term are zero
         if (!beta && a.t[0].upper && pad8(a.t[0].w) >= 8 * NT) {
-            launch_lds_kernel(update_pipe_kernel<T, MT, NT, SMAX, false, true>, grid, shmem, st, a, kpad,
+            launch_lds_kernel(update_pipe_kernel<T, MT, NT, SMAX, false, true>, grid, 256, shmem, st, a, kpad,
                               kpad / 8, nts);
             return;
         }
     }
     if (beta)
-        launch_lds_kernel(update_pipe_kernel<T, MT, NT, SMAX, true>, grid, shmem, st, a, kpad, kpad / 8, nts);
+        launch_lds_kernel(update_pipe_kernel<T, MT, NT, SMAX, true>, grid, 256, shmem, st, a, kpad, kpad / 8, nts);
     else
-        launch_lds_kernel(update_pipe_kernel<T, MT, NT, SMAX, false>, grid, shmem, st, a, kpad, kpad / 8, nts);
+        launch_lds_kernel(update_pipe_kernel<T, MT, NT, SMAX, false>, grid, 256, shmem, st, a, kpad, kpad / 8, nts);
 }
 
 // The pipelined kernel when the shape allows it (see update_pipe_kernel).

@@ -236,6 +236,42 @@ def test_gram_tall_blocks(device, bx, by, dtype):
     assert np.array_equal(Gm, G.gram(Xd, Yd).cpu().numpy())
 
 
+@pytest.mark.parametrize("wy,w", [(0, 9), (0, 48), (0, 64), (1, 7), (8, 8), (9, 15), (20, 44), (16, 48),
+                                  (48, 16), (57, 7)])
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_gram_against_own_columns(device, wy, w, dtype):
+    # [Y X]^H X with X the last columns of the same block: the shared-operand
+    # kernel, at unit and tile edges, with row counts around a K step, a wave's
+    # steps and a row block.  Each entry sums n products of FP64 accuracy:
+    # n eps of the sum of moduli bounds it.
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    tdt = torch.complex128 if dtype == "c128" else torch.complex64
+    g = torch.Generator(device="cpu").manual_seed(wy * 100 + w)
+    for n in (1, 3, 5, 63, 65, 129, 8195, 33001):
+        Z = torch.randn(n, wy + w + 2, dtype=tdt, generator=g).to(device)[:, 1:wy + w + 1]
+        Gm = G.gram(Z, Z[:, wy:]).cpu().numpy()
+        Zh = Z.cpu().numpy().astype(np.complex128)
+        ref = Zh.conj().T @ Zh[:, wy:]
+        scale = np.abs(Zh).T @ np.abs(Zh[:, wy:])
+        assert np.max(np.abs(Gm - ref) / scale) < 4 * (n + 4) * 2.3e-16, n
+        assert np.array_equal(Gm[wy:], Gm[wy:].conj().T), n
+
+
+def test_gram_of_rows_far_apart(device):
+    # a leading dimension whose rows lie further apart than the kernels' 32-bit
+    # offsets reach
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    ld, n = 90_000_000, 3
+    X = torch.zeros((n - 1) * ld + 8, dtype=torch.complex128, device=device).as_strided((n, 5), (ld, 1))
+    x = torch.randn(n, 5, dtype=torch.complex128, generator=torch.Generator().manual_seed(3))
+    X.copy_(x)
+    Gm = G.gram(X, X[:, 2:4]).cpu().numpy()
+    ref = x.numpy().conj().T @ x.numpy()[:, 2:4]
+    assert np.max(np.abs(Gm - ref)) < 1e-14 * np.max(np.abs(ref)) * n
+
+
 @pytest.mark.parametrize("wx,wy", [(1, 1), (7, 5), (10, 10), (16, 16), (40, 20), (30, 10), (10, 30),
                                    (64, 32), (64, 16), (48, 48), (16, 48), (33, 40), (128, 8)])
 @pytest.mark.parametrize("dtype", ["c128", "c64"])

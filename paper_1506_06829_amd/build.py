@@ -17,7 +17,7 @@ ROOT = PKG.parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libgplhr.so"
 
-SOURCES = ["kernels.hip", "gram_c64.hip", "gram_c128.hip", "gram.hip", "driver.hip", "capi.cpp", "memory.cpp", "small_dense.cpp"]
+SOURCES = ["kernels.hip", "gram_c64.hip", "gram_c128.hip", "gram.hip", "update_c64.hip", "update_c128.hip", "driver.hip", "capi.cpp", "memory.cpp", "small_dense.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = [
@@ -31,7 +31,7 @@ COMMON = [
 # back around every MFMA loop: a register-only FP64 MFMA loop ran at 36 TFLOP/s
 # in that form and at 77 in this one.
 MFMA_VGPR = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-EXTRA = {"gram_c64.hip": MFMA_VGPR, "gram_c128.hip": MFMA_VGPR}
+EXTRA = {f: MFMA_VGPR for f in ("gram_c64.hip", "gram_c128.hip", "update_c64.hip", "update_c128.hip")}
 # -fcx-limited-range: textbook complex multiply/divide (no NaN/Inf recovery
 # calls); the small dense step never sees magnitudes near the overflow range
 HOST_ONLY = ["-O3", "-std=c++17", "-fPIC", "-march=x86-64-v3", "-fcx-limited-range", f"-I{CSRC}"]
@@ -56,7 +56,7 @@ def build(verbose: bool = False) -> Path:
         raise RuntimeError("hipcc not found")
     build_dir = ROOT / "_build"
     build_dir.mkdir(exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(6, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(lambda s: _compile(s, build_dir), SOURCES))
     tmp = LIB.with_suffix(".so.tmp")
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", str(tmp), *map(str, objs)]

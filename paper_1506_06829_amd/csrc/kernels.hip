@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "device_math.h"
+#include "update.h"
 
 namespace gplhr {
 
@@ -398,23 +399,13 @@ void launch_reduce_partials(hipStream_t st, const double2 *part, int nblk, int b
 // ---------------------------------------------------------------------------
 // row-local block update
 // ---------------------------------------------------------------------------
-// Out = beta Out + Add + sum_t alpha_t diag(rs_t) In_t M_t, row by row.  Two
-// kernels compute it: a VALU kernel that gives each lane one row, and an MFMA
-// kernel that runs the complex product as one real GEMM.  Both read all
+// Out = beta Out + Add + sum_t alpha_t diag(rs_t) In_t M_t, row by row.
+// update_stream_kernel (update.h) takes up to 64 input columns.  The two kernels
+// here compute the rest: an MFMA kernel for wider inputs, a row scale together
+// with beta != 0, and blocks it cannot address; and a VALU kernel that gives
+// each lane one row, for a plain copy of Add, for narrow complex64 outputs of
+// wide inputs and for coefficients the MFMA kernel cannot stage.  All read the
 // inputs of a row before they write its outputs, so Out may alias any input.
-template <typename T>
-struct UpdArgs {
-    int64_t n;
-    T *out;
-    int ldo, wout, ocol, split, ocol2;
-    double2 beta;
-    int nterms;
-    UpdTerm<T> t[3];
-    int wtot;
-    const T *add;    // added block (column c at add[c]) or null
-    int ldadd;
-};
-
 
 // One wavefront per 64-row tile.  Input columns are staged through LDS in
 // chunks of CH with coalesced loads (consecutive lanes read consecutive
@@ -541,28 +532,6 @@ __global__ __launch_bounds__(64) void update_kernel(UpdArgs<T> a) {
 // the next PF slabs (across terms and row groups) are in flight while a slab
 // is multiplied.  FP64 blocks use the FP64 MFMA; complex64 blocks the FP32
 // one (FP32 accumulation, as in the VALU kernel).
-template <typename T> struct UpdMma;
-template <> struct UpdMma<double2> {
-    using R = double;
-    using V = d4v;
-    static __device__ __forceinline__ V mma(R a, R b, V c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    // accumulator register v of lane (i, k) holds output row 4v + k
-    static __device__ __forceinline__ int row(int v, int k) { return 4 * v + k; }
-};
-template <> struct UpdMma<float2> {
-    using R = float;
-    using V = f4v;
-    static __device__ __forceinline__ V mma(R a, R b, V c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    // accumulator register v of lane (i, k) holds output row 4k + v
-    static __device__ __forceinline__ int row(int v, int k) { return 4 * k + v; }
-};
-
-__host__ __device__ __forceinline__ int pad8(int w) { return (w + 7) & ~7; }
-
 struct UpdCursor {
     int64_t g;   // first row of the wavefront's row group
     int t, s;    // term, slab of 8 input columns within the term
@@ -742,335 +711,62 @@ static void launch_update_mfma(hipStream_t st, const UpdArgs<T> &a, int kpad) {
     hipLaunchKernelGGL((update_mfma_kernel<T, MT, NT, 2>), dim3(grid), dim3(256), shmem, st, a, kpad);
 }
 
-// Pipelined MFMA kernel for the streaming shapes (inputs at most 64 complex
-// columns, at most one row-scale vector).  A wavefront owns row groups of 16
-// MT rows, as in update_mfma_kernel, but loads all S slabs of its next row
-// group, and that group's Out rows when beta != 0, into a second register
-// buffer while it multiplies the current one, so a whole row group's reads are
-// in flight behind every multiply.  The product tile then passes through a
-// wave-private LDS tile and leaves as coalesced 16-byte chunks of Out rows
-// (one complex128 or two complex64 per lane), read-modify-write included.
-// Complex64 blocks need even widths, leading dimensions and column offsets
-// (16-byte input pairs and output chunks); the launcher checks that.
-template <typename T> struct UpdChunk;
-template <> struct UpdChunk<float2> { using C = float4; static constexpr int CPC = 2; };
-template <> struct UpdChunk<double2> { using C = double2; static constexpr int CPC = 1; };
-
-// LDS written by some lanes of a wavefront and then read by others: the
-// wavefront's LDS operations complete in order, and the fences keep the
-// compiler from moving them across this point.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-template <typename T, int MT, int NT>
-struct UpdPipeShape {
-    using R = typename UpdMma<T>::R;
-    static constexpr int WOP = 8 * NT;                         // complex output columns
-    static constexpr int ROWS = 16 * MT;                       // rows per row group
-    static constexpr int LDR = 2 * WOP + 16 / (int)sizeof(R);  // reals per LDS tile row
-    static constexpr int CPC = UpdChunk<T>::CPC;
-    static constexpr int CPR = WOP / CPC;                      // chunks per row
-    static constexpr int NCH = ROWS * CPR / 64;                // chunks per lane
-    static_assert((ROWS * CPR) % 64 == 0, "whole chunks per lane");
-    static size_t shmem(int kpad) {
-        return sizeof(T) * (size_t)kpad * WOP + (size_t)4 * ROWS * LDR * sizeof(R);
-    }
-};
-
-// BETA: Out is read (beta != 0); without it no Out buffer is held.
-// TRI: the coefficients of term 0 are upper triangular (M(k, j) = 0 for
-// k > j, as R^{-1} of a Cholesky-QR step) and fill at least NT slabs, so the
-// products of its slab i with the output tiles nt < i are zero and are not
-// formed.
-template <typename T, int MT, int NT, int SMAX, bool BETA, bool TRI = false>
-__global__ __launch_bounds__(256) void update_pipe_kernel(UpdArgs<T> a, int kpad, int nslab, int nts) {
-    using Sh = UpdPipeShape<T, MT, NT>;
-    using R = typename UpdMma<T>::R;
-    using V = typename UpdMma<T>::V;
-    using C = typename UpdChunk<T>::C;
-    constexpr int WOP = Sh::WOP, ROWS = Sh::ROWS, LDR = Sh::LDR, CPC = Sh::CPC, CPR = Sh::CPR,
-                  NCH = Sh::NCH;
-    extern __shared__ double2 sh_mfma_raw[];
-    T *sM = reinterpret_cast<T *>(sh_mfma_raw);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    R *sO = reinterpret_cast<R *>(sM + (size_t)kpad * WOP) + (size_t)wave * ROWS * LDR;
-    stage_update_coeffs(a, kpad, WOP, sM);
-    const int li = lane & 15, lk = lane >> 4;
-    const bool odd = li & 1;
-    // slab i of a row group: term st_t[i], its slab st_s[i], LDS row st_k[i]
-    int st_t[SMAX], st_s[SMAX], st_k[SMAX];
-    {
-        int t = 0, s = 0, k = 0;
-#pragma unroll
-        for (int i = 0; i < SMAX; ++i) {
-            while (t + 1 < a.nterms && s * 8 >= a.t[t].w) { s = 0; ++t; }
-            st_t[i] = t;
-            st_s[i] = s;
-            st_k[i] = k;
-            ++s;
-            k += 8;
+// update_stream_kernel (update.h) when the shape allows it: up to 64 input
+// columns (each term padded to 8), at most one row-scale vector and that only
+// when Out is overwritten, complex128 pointers aligned to their 16-byte entries,
+// row strides within the kernel's 32-bit offsets.
+template <typename T>
+static bool update_stream(hipStream_t st, UpdArgs<T> a, int kpad) {
+    if (a.nterms < 1 || kpad < 8 || kpad > 64 || a.add) return false;
+    auto al16 = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
+    auto far = [](int64_t ld) { return (16 * ld + 64) * (int64_t)sizeof(T) > (int64_t)UINT32_MAX; };
+    if (far(a.ldo) || a.n > ((int64_t)UINT32_MAX - 65536) * 16) return false;
+    bool pairs = al16(a.out) && !((a.wout | a.ocol | a.ocol2 | a.ldo) & 1) && !(a.split < a.wout && (a.split & 1));
+    UpdKind k{};
+    int ns = 0;
+    for (int t = 0; t < a.nterms; ++t) {
+        const UpdTerm<T> &tm = a.t[t];
+        if (far(tm.ld) || (tm.rowscale && a.rs && a.rs != tm.rowscale)) return false;
+        if (tm.rowscale) a.rs = tm.rowscale;
+        pairs = pairs && al16(tm.in) && !((tm.ld | tm.col | tm.w) & 1);
+        if (sizeof(T) == 16 && !al16(tm.in)) return false;
+        for (int s = 0; s * 8 < tm.w; ++s, ++ns) {
+            a.slab[ns].p = tm.in + tm.col + s * 8;
+            a.slab[ns].ldb = (int64_t)tm.ld * sizeof(T);
+            a.slab[ns].lim = std::min(8, tm.w - s * 8);
+            k.rag = k.rag || a.slab[ns].lim < 8;
+            if (tm.rowscale) a.scaled |= 1u << ns;
         }
     }
-    const T beta = from_d<T>(a.beta);
-    T bx[2][SMAX][MT][2];
-    C bd[2][BETA ? NCH : 1];
-    // the row scale of the terms that carry one (the launcher admits a single
-    // scale vector), loaded with the row group
-    const T *rsc = nullptr;
-    for (int t = 0; t < a.nterms; ++t)
-        if (a.t[t].rowscale) rsc = a.t[t].rowscale;
-    T brs[2][MT];
-    auto load = [&](int p, int64_t g) {
-        if (rsc) {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const int64_t row = g + mt * 16 + li;
-                brs[p][mt] = rsc[row < a.n ? row : a.n - 1];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < SMAX; ++i) {
-            if (i < nslab) {
-                const UpdTerm<T> &tm = a.t[st_t[i]];
-                const int col0 = st_s[i] * 8 + 2 * lk;
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    int64_t row = g + mt * 16 + li;
-                    row = row < a.n ? row : a.n - 1;
-                    const T *rp = tm.in + row * tm.ld + tm.col;
-                    if constexpr (sizeof(T) == 8) {
-                        // even width: entries col0 and col0 + 1 exist together
-                        const float4 v = *reinterpret_cast<const float4 *>(rp + (col0 < tm.w ? col0 : 0));
-                        bx[p][i][mt][0] = make_float2(v.x, v.y);
-                        bx[p][i][mt][1] = make_float2(v.z, v.w);
-                    } else {
-                        bx[p][i][mt][0] = rp[col0 < tm.w ? col0 : 0];
-                        bx[p][i][mt][1] = rp[col0 + 1 < tm.w ? col0 + 1 : 0];
-                    }
-                }
-            }
-        }
-        if constexpr (BETA) {
-#pragma unroll
-            for (int q = 0; q < NCH; ++q) {
-                const int e = q * 64 + lane;
-                const int rr = e / CPR, c0 = (e - rr * CPR) * CPC;
-                int64_t row = g + rr;
-                row = row < a.n ? row : a.n - 1;
-                const int c = c0 < a.wout ? c0 : 0;
-                const int oc = (c < a.split) ? (a.ocol + c) : (a.ocol2 + c - a.split);
-                bd[p][q] = *reinterpret_cast<const C *>(a.out + row * a.ldo + oc);
-            }
-        }
-    };
-    auto compute_store = [&](int p, int64_t g) {
-        V acc[MT][NT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = V{0, 0, 0, 0};
-#pragma unroll
-        for (int i = 0; i < SMAX; ++i) {
-            if (i < nslab) {
-                const UpdTerm<T> &tm = a.t[st_t[i]];
-                const int col0 = st_s[i] * 8 + 2 * lk;
-                const T *mrow = sM + (int64_t)(st_k[i] + 2 * lk) * WOP + (li >> 1);
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    T m[NT];
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        m[nt] = (TRI && i < NT && nt < i) ? czero<T>() : mrow[h * WOP + nt * 8];
-                    const bool ok = col0 + h < tm.w;
-                    const bool scaled = tm.rowscale != nullptr;
-                    T xs[MT];
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) {
-                        const T x = bx[p][i][mt][h];
-                        xs[mt] = scaled ? cmul(brs[p][mt], x) : x;
-                    }
-#pragma unroll
-                    for (int part = 0; part < 2; ++part) {
-                        R bv[NT];
-#pragma unroll
-                        for (int nt = 0; nt < NT; ++nt)
-                            bv[nt] = part == 0 ? (odd ? m[nt].y : m[nt].x) : (odd ? m[nt].x : -m[nt].y);
-#pragma unroll
-                        for (int mt = 0; mt < MT; ++mt) {
-                            const T x = xs[mt];
-                            const R av = ok ? (part == 0 ? x.x : x.y) : (R)0;
-#pragma unroll
-                            for (int nt = 0; nt < NT; ++nt)
-                                if (!(TRI && i < NT && nt < i))
-                                    acc[mt][nt] = UpdMma<T>::mma(av, bv[nt], acc[mt][nt]);
-                        }
-                    }
-                }
-            }
-        }
-        // tile -> LDS: register v of lane (li, lk) is real column nt * 16 + li
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    sO[(mt * 16 + UpdMma<T>::row(v, lk)) * LDR + nt * 16 + li] = acc[mt][nt][v];
-        wave_lds_sync();
-#pragma unroll
-        for (int q = 0; q < NCH; ++q) {
-            const int e = q * 64 + lane;
-            const int rr = e / CPR, c = (e - rr * CPR) * CPC;
-            const int64_t row = g + rr;
-            C o = *reinterpret_cast<const C *>(sO + rr * LDR + 2 * c);
-            if (row < a.n && c < a.wout) {
-                const int oc = (c < a.split) ? (a.ocol + c) : (a.ocol2 + c - a.split);
-                if (a.add) {
-                    const C ad = *reinterpret_cast<const C *>(a.add + row * a.ldadd + c);
-                    o.x += ad.x;
-                    o.y += ad.y;
-                    if constexpr (CPC == 2) { o.z += ad.z; o.w += ad.w; }
-                }
-                if constexpr (BETA) {
-                    const C d = bd[p][q];
-                    o.x += beta.x * d.x - beta.y * d.y;
-                    o.y += beta.x * d.y + beta.y * d.x;
-                    if constexpr (CPC == 2) {
-                        o.z += beta.x * d.z - beta.y * d.w;
-                        o.w += beta.x * d.w + beta.y * d.z;
-                    }
-                }
-                C *dst = reinterpret_cast<C *>(a.out + row * a.ldo + oc);
-                if (nts) {
-                    if constexpr (CPC == 2) {
-                        typedef float f4n __attribute__((ext_vector_type(4)));
-                        __builtin_nontemporal_store(f4n{o.x, o.y, o.z, o.w}, reinterpret_cast<f4n *>(dst));
-                    } else {
-                        typedef double d2n __attribute__((ext_vector_type(2)));
-                        __builtin_nontemporal_store(d2n{o.x, o.y}, reinterpret_cast<d2n *>(dst));
-                    }
-                } else {
-                    *dst = o;
-                }
-            }
-        }
-        // the next tile may overwrite sO only after every lane has read it
-        wave_lds_sync();
-    };
-    // row groups g0, g0 + stride, ...: buffer 0 holds the even ones, buffer 1
-    // the odd ones (static register indices)
-    const int64_t stride = (int64_t)gridDim.x * 4 * ROWS;
-    int64_t g = ((int64_t)blockIdx.x * 4 + wave) * ROWS;
-    if (g < a.n) load(0, g);
-    while (g < a.n) {
-        const int64_t g1 = g + stride;
-        if (g1 < a.n) load(1, g1);
-        compute_store(0, g);
-        g = g1;
-        if (g >= a.n) break;
-        const int64_t g2 = g + stride;
-        if (g2 < a.n) load(0, g2);
-        compute_store(1, g);
-        g = g2;
-    }
-}
-
-template <typename T, int MT, int NT, int SMAX>
-static void launch_update_pipe(hipStream_t st, const UpdArgs<T> &a, int kpad) {
-    const bool beta = (a.beta.x != 0.0 || a.beta.y != 0.0);
-    constexpr int64_t rows = 16 * MT;
-    const int64_t waves = (a.n + rows - 1) / rows;
-    // workgroups in flight, by measurement at 4096000 rows: 4096 for up to 4
-    // slabs per row group (16 -> 16 complex64 with beta = 1: 417 -> 299 us
-    // against update_mfma_kernel), 2048 for the wider ones whose register
-    // buffers are larger
-    const int cap = SMAX <= 4 ? 4096 : 2048;
-    const int grid = (int)std::min<int64_t>((waves + 3) / 4, cap);
+    if (sizeof(T) == 16 && !al16(a.out)) return false;
+    const int nt = (a.wout + 7) / 8;
+    k.beta = a.beta.x != 0.0 || a.beta.y != 0.0;
+    k.scl = a.rs != nullptr;
+    k.vec = sizeof(T) == 16 || pairs;
+    k.tri = a.t[0].upper && pad8(a.t[0].w) == 8 * nt;
+    const UpdFn<T> fn = update_pick<T>(nt, ns, k);
+    if (!fn) return false;
+    const size_t shmem = (size_t)ns * 4 * nt * 64 * sizeof(typename UpdMma<T>::R);
+    // Two waves per SIMD, persistent: more only spread the accesses (4096000
+    // rows, 32 -> 16 complex64: 286 us against 300 at three and 303 at four).  As
+    // one workgroup of eight waves per CU where the coefficients take more than
+    // 40 KiB of LDS and there are rows to spare (they are formed once per
+    // workgroup: 262144 rows, 56 -> 42 complex128 113 against 118 us), else as two
+    // of four (1024 rows, 64 -> 32 complex128: 10.9 against 13.9 us).
+    a.waves = shmem > 40 * 1024 && a.n >= 65536 ? 8 : 4;
+    const int bpc = a.waves == 8 ? 1 : 2;
+    const int rows = sizeof(T) == 8 && ns <= 2 ? 32 : 16;   // of a row group
+    const int64_t groups = (a.n + rows - 1) / rows;
+    const int grid = (int)std::min<int64_t>((groups + a.waves - 1) / a.waves, 256 * bpc);
+    a.nw = grid * a.waves;
     // outputs larger than the last-level caches stream past them
     const int nts = (double)a.n * a.wout * sizeof(T) > 256.0 * 1024 * 1024;
-    const size_t shmem = UpdPipeShape<T, MT, NT>::shmem(kpad);
-    if constexpr (MT == 1 && NT == 6 && SMAX == 8) {
-        // the Cholesky-QR shape of the test basis (48 columns from their
-        // upper triangular R^{-1} and 16 more): 15 of the 36 products of the
-        // triangular term are zero
-        if (!beta && a.t[0].upper && pad8(a.t[0].w) >= 8 * NT) {
-            launch_lds_kernel(update_pipe_kernel<T, MT, NT, SMAX, false, true>, grid, 256, shmem, st, a, kpad,
-                              kpad / 8, nts);
-            return;
-        }
-    }
-    if (beta)
-        launch_lds_kernel(update_pipe_kernel<T, MT, NT, SMAX, true>, grid, 256, shmem, st, a, kpad, kpad / 8, nts);
-    else
-        launch_lds_kernel(update_pipe_kernel<T, MT, NT, SMAX, false>, grid, 256, shmem, st, a, kpad, kpad / 8, nts);
-}
-
-// The pipelined kernel when the shape allows it (see update_pipe_kernel).
-template <typename T, int MT, int NT>
-static bool update_pipe_shape(hipStream_t st, const UpdArgs<T> &a, int kpad) {
-    if (UpdPipeShape<T, MT, NT>::shmem(kpad) > 160 * 1024) return false;
-    const int ns = kpad / 8;
-    if (ns <= 2) launch_update_pipe<T, MT, NT, 2>(st, a, kpad);
-    else if (ns <= 4) launch_update_pipe<T, MT, NT, 4>(st, a, kpad);
-    else if (ns <= 8) launch_update_pipe<T, MT, NT, 8>(st, a, kpad);
-    else return false;
+    launch_lds_kernel(fn, grid, a.waves * 64, shmem, st, a, ns, nts);
     return true;
 }
 
-template <typename T>
-static bool update_pipe(const UpdArgs<T> &a, int kpad, hipStream_t st) {
-    if (a.nterms < 1 || kpad < 8 || kpad > 64) return false;
-    auto al16 = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-    if (!al16(a.out) || (a.add && !al16(a.add))) return false;
-    const void *rs = nullptr;
-    for (int t = 0; t < a.nterms; ++t) {
-        const UpdTerm<T> &tm = a.t[t];
-        // one row-scale vector at most (the kernel holds one per row group)
-        if (tm.rowscale) {
-            if (rs && rs != tm.rowscale) return false;
-            rs = tm.rowscale;
-        }
-        if (!al16(tm.in)) return false;
-        if (sizeof(T) == 8 && ((tm.ld | tm.col | tm.w) & 1)) return false;
-    }
-    if (sizeof(T) == 8) {
-        if ((a.wout | a.ocol | a.ocol2 | a.ldo) & 1) return false;
-        if (a.split < a.wout && (a.split & 1)) return false;
-        if (a.add && (a.ldadd & 1)) return false;
-    }
-    const int nt = (a.wout + 7) / 8;
-    if constexpr (sizeof(T) == 8) {
-        // complex64 rows are half as long: two 16-row tiles per row group up
-        // to 4 slabs; from 5 slabs the register buffers of two tiles leave one
-        // wave per SIMD, and one tile per group is faster (48 + 16 -> 16 at
-        // 4096000 rows: 651 -> 551 us)
-        switch (nt) {
-            case 1: return kpad > 32 ? update_pipe_shape<T, 1, 1>(st, a, kpad) : update_pipe_shape<T, 2, 1>(st, a, kpad);
-            case 2: return kpad > 32 ? update_pipe_shape<T, 1, 2>(st, a, kpad) : update_pipe_shape<T, 2, 2>(st, a, kpad);
-            case 3: return update_pipe_shape<T, 1, 3>(st, a, kpad);
-            case 4: return update_pipe_shape<T, 1, 4>(st, a, kpad);
-            case 5: return update_pipe_shape<T, 1, 5>(st, a, kpad);
-            case 6: return update_pipe_shape<T, 1, 6>(st, a, kpad);
-            default: return false;
-        }
-    } else {
-        switch (nt) {
-            case 1: return update_pipe_shape<T, 1, 1>(st, a, kpad);
-            case 2: return update_pipe_shape<T, 1, 2>(st, a, kpad);
-            case 3: return update_pipe_shape<T, 1, 3>(st, a, kpad);
-            case 4: return update_pipe_shape<T, 1, 4>(st, a, kpad);
-            case 5: return update_pipe_shape<T, 1, 5>(st, a, kpad);
-            case 6: return update_pipe_shape<T, 1, 6>(st, a, kpad);
-            default: return false;
-        }
-    }
-}
-
-// MFMA or VALU kernel, by measurement on the solver's shapes (4096000 and
-// 262144 rows): in FP64 the MFMA kernel is as fast or faster for every shape;
+// MFMA or VALU kernel, by measurement at 4096000 and 262144 rows: in FP64 the
+// MFMA kernel is as fast or faster for every shape;
 // for complex64 it wins once the output is wider than 16 columns, Out is
 // accumulated into, or the output fills its 8- or 16-column tiles (16 -> 16
 // overwrite at 262144 rows: 25.8 -> 19.2 us, 48 -> 16: 50.4 -> 39.4 us); the
@@ -1133,7 +829,7 @@ void launch_update(hipStream_t st, int64_t n, T *out, int ldo, int wout, int oco
     a.wtot = wtot;
     int kpad = 0;
     for (int t = 0; t < nterms; ++t) kpad += pad8(terms[t].w);
-    if (update_pipe<T>(a, kpad, st) || update_mfma<T>(a, kpad, st)) {
+    if (update_stream<T>(st, a, kpad) || update_mfma<T>(a, kpad, st)) {
         GPLHR_HIP_CHECK(hipGetLastError());
         return;
     }

@@ -333,6 +333,45 @@ def test_block_update_even_strides(device, wx, wy, dtype, beta):
         assert np.array_equal(rest[:, wy + 4:], Y0[:, wy + 4:].astype(rest.dtype))
 
 
+@pytest.mark.parametrize("wx,wy,off", [(1, 1, 0), (9, 9, 0), (8, 16, 1), (16, 24, 0), (24, 17, 1), (41, 33, 0),
+                                       (42, 42, 0), (57, 40, 1), (64, 48, 0)])
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("beta", [0.0, -0.5 + 1.0j])
+def test_block_update_row_groups(device, wx, wy, off, dtype, beta):
+    # row counts around a row group and a workgroup's groups, ragged slabs and
+    # tiles, blocks inside NaN-filled storage at even and odd column offsets:
+    # nothing outside the block is read into a result or written.  wx products
+    # and beta Y per entry: (wx + 4) eps of the sum of moduli bounds each part.
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    tdt, eps = (torch.complex128, 2.3e-16) if dtype == "c128" else (torch.complex64, 1.2e-7)
+    g = torch.Generator(device="cpu").manual_seed(wx * 100 + wy)
+    nan = complex(float("nan"), float("nan"))
+    for n in (1, 15, 17, 33, 64, 129, 4097, 33003):
+        Xs = torch.full((n, wx + 4), nan, dtype=tdt)
+        Ys = torch.full((n, wy + 4), nan, dtype=tdt)
+        Xs[:, off:off + wx] = torch.randn(n, wx, dtype=tdt, generator=g)
+        Ys[:, off:off + wy] = torch.randn(n, wy, dtype=tdt, generator=g)
+        if n > 20:
+            Xs[7, off] = complex(float("inf"), 0.0)      # one bad row stays one
+        M = torch.randn(wx, wy, dtype=torch.complex128, generator=g)
+        Xd, Yd = Xs.to(device), Ys.to(device)
+        G.block_update(Xd[:, off:off + wx], M.to(device), Yd[:, off:off + wy], beta=beta)
+        out = Yd.cpu().numpy()
+        x = Xs[:, off:off + wx].numpy().astype(np.complex128)
+        y = Ys[:, off:off + wy].numpy().astype(np.complex128)
+        rows = np.ones(n, bool)
+        if n > 20:
+            rows[7] = False
+            assert not np.isfinite(out[7, off:off + wy]).any()
+        with np.errstate(invalid="ignore"):
+            ref = beta * y + x @ M.numpy()
+            scale = abs(beta) * np.abs(y) + np.abs(x) @ np.abs(M.numpy())
+        err = np.abs(out[:, off:off + wy] - ref)[rows] / scale[rows]
+        assert err.max() < 2 * (wx + 4) * eps, n
+        assert np.isnan(out[:, :off]).all() and np.isnan(out[:, off + wy:]).all()
+
+
 @pytest.mark.parametrize("w", [10, 16, 48])
 @pytest.mark.parametrize("dtype", ["c128", "c64"])
 def test_block_update_in_place(device, w, dtype):

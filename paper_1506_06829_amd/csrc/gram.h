@@ -80,10 +80,19 @@ constexpr int gram_groups(int tiles) { return tiles <= 17 ? 1 : tiles <= 34 ? 2 
 constexpr int gram_groups(int ma, int mb, int a1, bool tri) {
     return gram_groups(tri && a1 == 0 && ma <= 5 ? ma * mb : gram_tiles(ma, mb, a1, tri));
 }
-// Four groups of an even by even product: quadrants, which read fewer units
-// than ranges of the list and share one body.
-constexpr bool gram_quads(int ma, int mb, bool tri) {
-    return !tri && ma % 2 == 0 && mb % 2 == 0 && gram_groups(ma * mb) == 4;
+// Four groups of a rectangular product: quadrants (of an odd unit count, halves
+// that share the middle unit), which read fewer units than ranges of the list
+// and share one body, so that the registers of several bodies don't add up.
+// Ranges stay where they fit without spilling and share less work (2000000 rows,
+// us as ranges / as quadrants): complex128, 56 x 56 1043 / 1086; complex64, 56 x 40
+// 706 / 806, scaled 56 x 56 1007 / 1090.  Elsewhere quadrants: complex128, 56 x 40
+// 1322 / 835, 64 x 40 1050 / 845, 64 x 56 2565 / 1145, scaled 56 x 56 2313 / 1170;
+// complex64, 64 x 56 2069 / 985, 56 x 56 1166 / 982.
+template <typename T>
+constexpr bool gram_quads(int ma, int mb, bool tri, bool scaled) {
+    if (tri || gram_groups(ma * mb) != 4) return false;
+    if (ma % 2 == 0 && mb % 2 == 0) return true;
+    return sizeof(T) == 16 ? ma != mb || scaled : mb == 7 && !scaled;
 }
 
 struct GramPlan {
@@ -122,12 +131,12 @@ constexpr int gram_pf() {
     for (int g = 0; g < G; ++g) {
         const GramPlan p = gram_plan<MA, MB, A1, TRI>(g);
         int c = 0;
-        for (int i = 0; i < 9; ++i) c += p.ua[i] + p.ub[i] * (i >= SC0 ? 2 : 1);
+        for (int i = 0; i < 9; ++i) c += p.ua[i] + p.ub[i];
         if (c > most) most = c;
         if (p.n > tiles) tiles = p.n;
     }
     const int regs = most * (int)sizeof(T) / 8 + (SC0 < MB ? (int)sizeof(T) / 4 : 0);
-    const int pf = (tiles > 12 ? G == 4 && !gram_quads(MA, MB, TRI) ? 30 : 40 : 56) / regs;
+    const int pf = (tiles > 12 ? G == 4 && !gram_quads<T>(MA, MB, TRI, SC0 < MB) ? 30 : 40 : 56) / regs;
     return pf < 2 ? 2 : pf > 8 ? 8 : pf;
 }
 
@@ -204,6 +213,16 @@ __global__ __launch_bounds__(1024) void gram_reduce_kernel(GramArgs<T> a) {
     }
 }
 
+// The value of lane l ^ 1: the other part of the complex entry whose real (even
+// lane) or imaginary part this lane holds.
+__device__ __forceinline__ float other_part(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double other_part(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0xb1, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), 0xb1, 0xf, 0xf, false));
+}
+
 // The rows of one wave: tile group GI, every KS-th K step.  M1: B units of the
 // first part (MB: Y alone); SC0: the first B unit that takes the row scale (MB:
 // none); u0, v0: the first unit of A and of B (quadrants).
@@ -233,7 +252,7 @@ __device__ __forceinline__ void gram_rows(const GramArgs<T> &a, int kh, int u0, 
     const char *py = TRI ? nullptr : reinterpret_cast<const char *>(a.Y + rb * a.ldy) + v0 * US;
     const char *pz = TWO ? reinterpret_cast<const char *>(a.Y2 + rb * a.ldy2) : nullptr;
     const char *ps = SC ? reinterpret_cast<const char *>(a.yscale + rb) : nullptr;
-    R va[PF][9], vb[PF][9], vo[PF][9];   // A, B, and the other part of scaled B entries
+    R va[PF][9], vb[PF][9];
     T vs[PF];
     // the operands of the K step at the running pointers, which then move on
     // by `rows`; back: rows to step back (the masked tail)
@@ -254,7 +273,6 @@ __device__ __forceinline__ void gram_rows(const GramArgs<T> &a, int kh, int u0, 
                     const uint32_t o = z ? (l ? ozl : oz) : (l ? oyl : oy);
                     const int imm = l ? 0 : (z ? u - M1 : u) * US;
                     vb[p][u] = get(z ? pz : py, o, imm, z ? a.ldy2 : a.ldy);
-                    if (u >= SC0) vo[p][u] = get(z ? pz : py, o ^ (uint32_t)sizeof(R), imm, z ? a.ldy2 : a.ldy);
                 }
         }
         if constexpr (SC) vs[p] = *reinterpret_cast<const T *>(ps - back * (int64_t)sizeof(T) + (uint32_t)(lk * sizeof(T)));
@@ -279,7 +297,7 @@ __device__ __forceinline__ void gram_rows(const GramArgs<T> &a, int kh, int u0, 
             for (int u = 0; u < MB; ++u)
                 if (P.ub[u]) {
                     double v = (double)vb[p][u];
-                    if (u >= SC0) v = sr * v + si * (double)vo[p][u];
+                    if (u >= SC0) v = sr * v + si * (double)other_part(vb[p][u]);
                     xb[u] = ok ? v : 0.0;
                 }
         }
@@ -325,7 +343,8 @@ template <typename T, int MA, int MB, int A1, bool TRI, int M1, int SC0>
 __global__ __launch_bounds__(GRAM_THREADS) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void gram_kernel(GramArgs<T> a) {
     constexpr int NT = gram_tiles(MA, MB, A1, TRI), G = gram_groups(MA, MB, A1, TRI), KS = 4 / G;
-    constexpr int TMAX = (NT + G - 1) / G;
+    constexpr bool QUADS = gram_quads<T>(MA, MB, TRI, SC0 < MB);
+    constexpr int TMAX = QUADS ? ((MA + 1) / 2) * ((MB + 1) / 2) : (NT + G - 1) / G;
     __shared__ double red[G == 4 ? 256 : G * 8 * 256];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int kh = wave / G, g = wave - kh * G;
@@ -334,15 +353,18 @@ void gram_kernel(GramArgs<T> a) {
     for (int t = 0; t < TMAX; ++t) acc[t] = d4v{0.0, 0.0, 0.0, 0.0};
     double *part = a.part + (int64_t)blockIdx.x * NT * 256;
     // the block's partial: register v of lane 16 k + c holds entry (4 v + k, c)
-    if constexpr (gram_quads(MA, MB, TRI)) {
-        constexpr int HA = MA / 2, HB = MB / 2;
-        const int u0 = (g & 1) * HA, v0 = (g >> 1) * HB;
+    if constexpr (QUADS) {
+        constexpr int HA = (MA + 1) / 2, HB = (MB + 1) / 2;
+        const int u0 = (g & 1) * (MA - HA), v0 = (g >> 1) * (MB - HB);
         gram_rows<T, HA, HB, HA, false, HB, SC0 ? HB : 0, 0, 1>(a, kh, u0, v0, acc);
 #pragma unroll
-        for (int t = 0; t < HA * HB; ++t)
+        for (int t = 0; t < HA * HB; ++t) {
+            // a shared middle unit is the first halves'
+            if ((MA % 2 && (g & 1) && t % HA == 0) || (MB % 2 && (g >> 1) && t < HA)) continue;
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 part[(u0 + t % HA + (v0 + t / HA) * MA) * 256 + v * 64 + lane] = acc[t][v];
+        }
     } else if constexpr (G == 4) {
         if (g == 0) gram_rows<T, MA, MB, A1, TRI, M1, SC0, 0, 1>(a, kh, 0, 0, acc);
         if (g == 1) gram_rows<T, MA, MB, A1, TRI, M1, SC0, 1, 1>(a, kh, 0, 0, acc);

@@ -258,6 +258,24 @@ def test_gram_against_own_columns(device, wy, w, dtype):
         assert np.array_equal(Gm[wy:], Gm[wy:].conj().T), n
 
 
+@pytest.mark.parametrize("bx,by", [(49, 49), (56, 56), (53, 40), (49, 48), (64, 33), (64, 49), (50, 63)])
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_gram_of_odd_unit_counts(device, bx, by, dtype):
+    # halves of an odd number of 8-column units overlap in the middle one; the
+    # last rows end the allocation.  Bound as above: n products per entry.
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    tdt = torch.complex128 if dtype == "c128" else torch.complex64
+    g = torch.Generator(device="cpu").manual_seed(bx * 100 + by)
+    for n in (1, 3, 63, 65, 33001):
+        Xd = torch.randn(n, bx, dtype=tdt, generator=g).to(device)
+        Yd = torch.randn(n, by, dtype=tdt, generator=g).to(device)
+        Gm = G.gram(Xd, Yd).cpu().numpy()
+        X, Y = Xd.cpu().numpy().astype(np.complex128), Yd.cpu().numpy().astype(np.complex128)
+        scale = np.abs(X).T @ np.abs(Y)
+        assert np.max(np.abs(Gm - X.conj().T @ Y) / scale) < 4 * (n + 4) * 2.3e-16, n
+
+
 def test_gram_of_rows_far_apart(device):
     # a leading dimension whose rows lie further apart than the kernels' 32-bit
     # offsets reach

@@ -360,6 +360,23 @@ def test_converged_parity_block_shapes(device, k, block, locking):
     assert match_err(lam[:k], ref.lam[:k]) < 1e-10
 
 
+@pytest.mark.parametrize("block", [13, 14])
+def test_converged_parity_of_a_wide_trial_space(device, block):
+    # 52 and 56 trial columns and a diagonal B: the projected pencil's Gram
+    # takes the row scale with seven 8-column units
+    p = problems.config("d1", 3000)
+    p.k, p.block = 5, block
+    p.V0 = problems.start_block(p.n, block)
+    s, _, _ = gpu_solver(p, max_iter=200)
+    st, nconv, res = s.iterate()
+    lam = s.lam()
+    s.close()
+    assert st == 0 and nconv == 5 and res <= 1e-10
+    ref = O.solve_problem(p, tol=1e-10, maxit=200)
+    assert ref.converged
+    assert match_err(lam[:5], ref.lam[:5]) < 1e-10
+
+
 def test_smallest_size_fills_the_space(device):
     # n = (m + 3) b: the second iteration's trial subspace is the whole space,
     # so its Rayleigh-Ritz values are exact eigenvalues (dense zggev)

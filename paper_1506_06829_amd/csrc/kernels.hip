@@ -859,42 +859,69 @@ template void launch_update<float2>(hipStream_t, int64_t, float2 *, int, int, in
                                     int);
 
 // ---------------------------------------------------------------------------
-// Cholesky-QR factor (one workgroup, w <= 64)
+// Cholesky-QR factor (one workgroup, w <= 16 NT)
 // ---------------------------------------------------------------------------
+// One matrix, held in registers by 16 x 16 threads (thread (r, c): the entries
+// (r + 16 a, c + 16 b)): its upper triangle is the scaled Gram and becomes
+// D R_1 with G = R_1^H D R_1, R_1 unit upper; its strict lower triangle starts as
+// zero and becomes R_1^{-H}, by the same row operations applied to the identity,
+// so that no substitution follows the factorisation.
+//
+// What bounds it: the chain of w steps, each an LDS write of the pivot row, a
+// barrier, its read back and a reciprocal (about 0.4 us); the arithmetic is spread
+// over the threads, masks are selects (branches cost 8 %), and the square roots
+// are taken after the last step.  Against a factorisation in LDS with a substitution
+// behind it (us, before -> now): w = 48 beside 16 columns 93 -> 28, the 66 factors
+// of a 10-pair solve with blocks of 14 27.5 -> 12 on average, the 164 of a
+// gradient with blocks of 8 13.5 -> 6.7.
+template <int NT>
 __global__ __launch_bounds__(256) void chol_rinv_kernel(int w, const double2 *G, double2 *Rinv,
                                                         int *status, double2 *Rout, int wy,
                                                         double2 *Cy, int guard) {
-    // A holds the scaled Gram; its upper triangle becomes R (A = R^H R) and
-    // its strict lower triangle then receives R^{-1} transposed (the diagonal
-    // of R^{-1} goes to dinv).
-    __shared__ double2 A[48 * 49];   // leading dimension w + 1: a row of A spreads over the LDS banks
-    __shared__ double2 GY[1024];     // G_Y (wy-by-w, column-major, ld wy): wy * w <= 1024
-    __shared__ double dsc[48];
-    __shared__ double rdiag[48];
-    __shared__ double dinv[48];
+    constexpr int N = 16 * NT, LD = N + 1;   // odd leading dimension: rows spread over the LDS banks
+    __shared__ double2 S[N * LD];            // R^{-1} (column-major)
+    __shared__ double2 GY[1024 + 48];        // G_Y (wy-by-w, row-major, odd leading dimension): wy * w <= 1024
+    __shared__ double2 row[2][N];
+    __shared__ double dsc[N], rdiag[N], dinv[N];
     __shared__ int flag;
-    const int tid = threadIdx.x;
-    const int lda = w + 1;
+    const int tid = threadIdx.x, r = tid & 15, c = tid >> 4;
+    const int ldy = w | 1;
+    double2 v[NT][NT];
     if (tid == 0) flag = 0;
-    if (wy == 0) {
-        for (int e = tid; e < w * w; e += 256) A[e % w + (e / w) * lda] = G[e];
-    } else {
-        // G is [Y X]^H X ((wy + w)-by-w, leading dimension wy + w) for an
-        // orthonormal Y: rows 0..wy-1 hold G_Y = Y^H X, the rest X^H X.  The
-        // Gram of the projected block (X - Y G_Y) is X^H X - G_Y^H G_Y.  G_Y
-        // is read into LDS once (the sums below and Cy read it many times).
-        const int ldg = wy + w;
-        for (int e = tid; e < wy * w; e += 256) GY[e] = G[e % wy + (size_t)(e / wy) * ldg];
+    // G is X^H X, or [Y X]^H X ((wy + w)-by-w, leading dimension wy + w) for an
+    // orthonormal Y: rows 0..wy-1 hold G_Y = Y^H X, the rest X^H X.  The
+    // Gram of the projected block (X - Y G_Y) is X^H X - G_Y^H G_Y.
+    const int ldg = wy + w;
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+            const int i = r + 16 * a, j = c + 16 * b;
+            v[a][b] = i <= j && j < w ? G[wy + i + (size_t)j * ldg] : make_double2(0.0, 0.0);
+        }
+    double full[NT];
+#pragma unroll
+    for (int a = 0; a < NT; ++a) full[a] = v[a][a].x;
+    if (wy > 0) {
+        for (int e = tid; e < wy * w; e += 256) {
+            const int t = e % wy, j = e / wy;
+            GY[t * ldy + j] = G[t + (size_t)j * ldg];
+        }
         __syncthreads();
-        for (int e = tid; e < w * w; e += 256) {
-            const int i = e % w, j = e / w;
-            double2 v = G[wy + i + (size_t)j * ldg];
-            for (int t = 0; t < wy; ++t) {
-                const double2 a = GY[t + i * wy], c = GY[t + j * wy];
-                v.x -= a.x * c.x + a.y * c.y;   // conj(a) * c
-                v.y -= a.x * c.y - a.y * c.x;
+        for (int t = 0; t < wy; ++t) {
+            double2 x[NT], y[NT];
+#pragma unroll
+            for (int a = 0; a < NT; ++a) {
+                x[a] = GY[t * ldy + min(r + 16 * a, w - 1)];
+                y[a] = GY[t * ldy + min(c + 16 * a, w - 1)];
             }
-            A[i + j * lda] = v;
+#pragma unroll
+            for (int a = 0; a < NT; ++a)
+#pragma unroll
+                for (int b = a; b < NT; ++b) {
+                    v[a][b].x -= x[a].x * y[b].x + x[a].y * y[b].y;   // conj(x) * y
+                    v[a][b].y -= x[a].x * y[b].y - x[a].y * y[b].x;
+                }
         }
     }
     __syncthreads();
@@ -904,160 +931,159 @@ __global__ __launch_bounds__(256) void chol_rinv_kernel(int w, const double2 *G,
         // lost more than half of its digits.  The pass then only projects
         // (Rinv = I, Cy = -G_Y, i.e. X <- X - Y G_Y exactly as block
         // Gram-Schmidt) and leaves the normalisation to the next pass.
-        if (tid < w) {
-            const double full = G[wy + tid + (size_t)tid * (wy + w)].x;
-            if (full > 0.0 && isfinite(full) && !(A[tid + tid * lda].x > 1e-8 * full)) flag = -1;
-        }
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+            if (r == c && r + 16 * a < w && full[a] > 0.0 && isfinite(full[a]) && !(v[a][a].x > 1e-8 * full[a]))
+                flag = -1;
         __syncthreads();
         if (flag < 0) {
             for (int e = tid; e < w * w; e += 256)
                 Rinv[e] = make_double2((e % w) == (e / w) ? 1.0 : 0.0, 0.0);
             for (int e = tid; e < wy * w; e += 256) {
-                const double2 g = GY[e];
+                const double2 g = GY[(e % wy) * ldy + e / wy];
                 Cy[e] = make_double2(-g.x, -g.y);
             }
             return;
         }
     }
-    if (tid < w) {
-        const double g = A[tid + tid * lda].x;
-        const bool ok = (g > 0.0) && isfinite(g);
-        dsc[tid] = ok ? 1.0 / sqrt(g) : 1.0;
-        if (!ok) atomicAdd(&flag, 1);
-    }
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+        if (r == c) {
+            const double g = v[a][a].x;
+            const bool ok = (g > 0.0) && isfinite(g);
+            dsc[r + 16 * a] = ok ? 1.0 / sqrt(g) : 1.0;
+            if (!ok && r + 16 * a < w) atomicAdd(&flag, 1);
+        }
     __syncthreads();
-    for (int e = tid; e < w * w; e += 256) {
-        const int i = e % w, j = e / w;
-        A[i + j * lda].x *= dsc[i] * dsc[j];
-        A[i + j * lda].y *= dsc[i] * dsc[j];
-    }
-    __syncthreads();
-    // right-looking Cholesky with one barrier per column: every thread takes
-    // the pivot itself, and row j enters the trailing update scaled on the
-    // fly (the rows are scaled in place once the factorisation is done)
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+            const double d = dsc[r + 16 * a] * dsc[c + 16 * b];
+            // (the lower triangle stays zero, whatever the scale)
+            if (r + 16 * a <= c + 16 * b) v[a][b] = make_double2(v[a][b].x * d, v[a][b].y * d);
+            else v[a][b] = make_double2(0.0, 0.0);
+        }
+    // step j: rows i > j of [Gram | identity] lose conj(g_ji) / g_jj times row
+    // j, whose entry j stands for the identity's (1)
     const double tol = 64.0 * 2.220446049250313e-16;
-    auto pivot = [&](int j) {
-        const double piv = A[j + j * lda].x;
-        // shifted factor below the tolerance; the second Cholesky-QR pass
-        // restores orthogonality
-        return (!(piv > tol) || !isfinite(piv)) ? tol : piv;
-    };
-    for (int j = 0; j < w; ++j) {
-        const double piv = A[j + j * lda].x;
-        if (tid == 0 && (!(piv > tol) || !isfinite(piv))) flag += 1;
-        const double rs = 1.0 / sqrt(pivot(j));
-        const int m = w - j - 1;
-        // the upper triangle of the trailing block, entry e -> (a, b), a <= b
-        for (int e = tid; e < m * (m + 1) / 2; e += 256) {
-            int b = (int)((sqrtf(8.0f * e + 1.0f) - 1.0f) * 0.5f);
-            if ((b + 1) * (b + 2) / 2 <= e) ++b;
-            if (b * (b + 1) / 2 > e) --b;
-            const int a = e - b * (b + 1) / 2;
-            const int ii = j + 1 + a, cc = j + 1 + b;
-            const double2 av = A[j + ii * lda], c = A[j + cc * lda];
-            const double2 ri = make_double2(av.x * rs, av.y * rs), rc = make_double2(c.x * rs, c.y * rs);
-            double2 v = A[ii + cc * lda];
-            v.x -= ri.x * rc.x + ri.y * rc.y;   // conj(ri) * rc
-            v.y -= ri.x * rc.y - ri.y * rc.x;
-            A[ii + cc * lda] = v;
-        }
-        __syncthreads();
-    }
-    if (tid < w) rdiag[tid] = sqrt(pivot(tid));
-    __syncthreads();
-    for (int e = tid; e < w * w; e += 256) {
-        const int i = e % w, c = e / w;
-        double2 &ae = A[i + c * lda];
-        if (i < c) {
-            const double r = 1.0 / rdiag[i];
-            ae = make_double2(ae.x * r, ae.y * r);
-        } else if (i == c) {
-            ae = make_double2(rdiag[i], 0.0);
-            dinv[i] = 1.0 / rdiag[i];
-        }
-    }
-    __syncthreads();
-    // R^{-1} by back substitution, one column per group of 4 lanes of a
-    // wavefront (no barriers): Rinv(i,j) = -(sum_{l=i+1..j} R(i,l) Rinv(l,j))
-    // / R(i,i), kept at A[j + i*lda]; lane q of the group sums the terms with
-    // l = q mod 4 and the group adds its partial sums with lane swaps, so all
-    // four lanes hold (and store) the same value
-    {
-        const int j = tid >> 2, q = tid & 3;
-        // the four lanes of a group share j, so they take the same branch
-        // and the same trip counts
-        if (j < w) for (int i = j - 1; i >= 0; --i) {
-            double2 s = make_double2(0.0, 0.0);
-            if (q == 0) {
-                const double2 r0 = A[i + j * lda];
-                s = make_double2(r0.x * dinv[j], r0.y * dinv[j]);
+    int bad = 0;
+    double pv = 1.0;   // the pivot of column tid
+#pragma unroll
+    for (int jb = 0; jb < NT; ++jb) {
+        const int je = min(16, w - 16 * jb);
+        for (int jj = 0; jj < je; ++jj) {
+            const int j = 16 * jb + jj;
+            double2 *rw = row[jj & 1];
+            if (r == jj)
+#pragma unroll
+                for (int b = 0; b < NT; ++b) rw[c + 16 * b] = v[jb][b];
+            __syncthreads();
+            double2 f[NT], x[NT];
+            double p = rw[j].x;
+#pragma unroll
+            for (int a = jb; a < NT; ++a) f[a] = rw[r + 16 * a];
+#pragma unroll
+            for (int b = 0; b < NT; ++b) x[b] = rw[c + 16 * b];
+            if (c == jj) x[jb] = make_double2(1.0, 0.0);
+            // shifted factor below the tolerance; the second Cholesky-QR pass
+            // restores orthogonality
+            const bool low = !(p > tol) || !isfinite(p);
+            p = low ? tol : p;
+            bad += low;
+            pv = tid == j ? p : pv;
+            // 1 / p, p in [tol, about 1], to an ulp
+            double inv = __builtin_amdgcn_rcp(p);
+            inv = fma(fma(-p, inv, 1.0), inv, inv);
+            inv = fma(fma(-p, inv, 1.0), inv, inv);
+#pragma unroll
+            for (int b = 0; b < NT; ++b) {
+                x[b].x *= inv;
+                x[b].y *= inv;
             }
-            for (int l = i + 1 + q; l < j; l += 4) {
-                const double2 r = A[i + l * lda];
-                const double2 x = A[j + l * lda];
-                s.x += r.x * x.x - r.y * x.y;
-                s.y += r.x * x.y + r.y * x.x;
+#pragma unroll
+            for (int a = jb; a < NT; ++a) {
+#pragma unroll
+                for (int b = 0; b < NT; ++b) {
+                    if (a > b && b > jb) continue;   // columns j < q < i: zero so far
+                    const bool in = (a > jb || r > jj) && (a > b ? b < jb || c <= jj :
+                                                           a < b || c >= r || (b == jb && c <= jj));
+                    const double2 o = v[a][b];   // conj(f) * x
+                    const double nx = fma(-f[a].y, x[b].y, fma(-f[a].x, x[b].x, o.x));
+                    const double ny = fma(f[a].y, x[b].x, fma(-f[a].x, x[b].y, o.y));
+                    v[a][b] = make_double2(in ? nx : o.x, in ? ny : o.y);
+                }
             }
-            s.x += __shfl_xor(s.x, 1);
-            s.y += __shfl_xor(s.y, 1);
-            s.x += __shfl_xor(s.x, 2);
-            s.y += __shfl_xor(s.y, 2);
-            A[j + i * lda] = make_double2(-s.x * dinv[i], -s.y * dinv[i]);
         }
     }
     __syncthreads();
-    // X Rinv with Rinv = D R_s^{-1}
-    for (int e = tid; e < w * w; e += 256) {
-        const int i = e % w, j = e / w;
-        double2 v = make_double2(0.0, 0.0);
-        if (i == j)
-            v = make_double2(dinv[i], 0.0);
-        else if (i < j)
-            v = A[j + i * lda];
-        Rinv[e] = make_double2(v.x * dsc[i], v.y * dsc[i]);
-        if (Rout) {
-            // G = D^{-1} R_s^H R_s D^{-1}: R = R_s D^{-1}
-            double2 r = make_double2(0.0, 0.0);
-            if (i <= j) r = make_double2(A[i + j * lda].x / dsc[j], A[i + j * lda].y / dsc[j]);
-            Rout[e] = r;
-        }
+    if (tid < w) {
+        const double d = sqrt(pv);
+        rdiag[tid] = d;
+        dinv[tid] = 1.0 / d;
     }
-    if (wy > 0) {
-        // Cy = -G_Y Rinv (wy-by-w, leading dimension wy): the coefficients of
-        // Y in (X - Y G_Y) Rinv; Rinv(i, j) = dsc[i] * (dinv[i] if i == j,
-        // A[j + i lda] if i < j)
-        for (int e = tid; e < wy * w; e += 256) {
-            const int r = e % wy, j = e / wy;
+    __syncthreads();
+    // R_s = D^{1/2} R_1, R_s^{-1} = (D^{-1/2} R_1^{-H})^H; X Rinv with
+    // Rinv = D_s R_s^{-1}, D_s the scale of the Gram
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+            const int i = r + 16 * a, j = c + 16 * b;
+            if (i >= w || j >= w) continue;
+            const double2 e = make_double2(v[a][b].x * dinv[i], v[a][b].y * dinv[i]);
+            if (i > j) S[j + i * LD] = make_double2(e.x * dsc[j], -e.y * dsc[j]);
+            else if (i == j) S[i + i * LD] = make_double2(dinv[i] * dsc[i], 0.0);
+            if (Rout) {
+                // G = D_s^{-1} R_s^H R_s D_s^{-1}: R = R_s D_s^{-1}
+                double2 o = make_double2(0.0, 0.0);
+                if (i < j) o = make_double2(e.x / dsc[j], e.y / dsc[j]);
+                else if (i == j) o = make_double2(rdiag[i] / dsc[i], 0.0);
+                Rout[i + j * w] = o;
+            }
+        }
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) {
+            const int i = r + 16 * a, j = c + 16 * b;
+            if (i < w && j < w) Rinv[i + j * w] = i <= j ? S[i + j * LD] : make_double2(0.0, 0.0);
+        }
+    // Cy = -G_Y Rinv (wy-by-w, leading dimension wy): the coefficients of
+    // Y in (X - Y G_Y) Rinv
+    for (int t = r; t < wy; t += 16)
+        for (int j = c; j < w; j += 16) {
             double2 acc = make_double2(0.0, 0.0);
+#pragma unroll 4
             for (int i = 0; i <= j; ++i) {
-                const double2 ri = (i == j) ? make_double2(dinv[i] * dsc[i], 0.0)
-                                            : make_double2(A[j + i * lda].x * dsc[i], A[j + i * lda].y * dsc[i]);
-                const double2 g = GY[r + i * wy];
+                const double2 ri = S[i + j * LD], g = GY[t * ldy + i];
                 acc.x += g.x * ri.x - g.y * ri.y;
                 acc.y += g.x * ri.y + g.y * ri.x;
             }
-            Cy[e] = make_double2(-acc.x, -acc.y);
+            Cy[t + j * wy] = make_double2(-acc.x, -acc.y);
         }
-    }
-    __syncthreads();
-    if (tid == 0 && flag > 0 && status) atomicAdd(status, flag);
+    if (tid == 0 && status && flag + bad > 0) atomicAdd(status, flag + bad);
+}
+
+static void launch_chol(hipStream_t st, int w, const double2 *G, double2 *Rinv, int *status,
+                        double2 *Rout, int wy, double2 *Cy, int guard) {
+    const auto fn = w <= 16 ? chol_rinv_kernel<1> : w <= 32 ? chol_rinv_kernel<2> : chol_rinv_kernel<3>;
+    hipLaunchKernelGGL(fn, dim3(1), dim3(256), 0, st, w, G, Rinv, status, Rout, wy, Cy, guard);
+    GPLHR_HIP_CHECK(hipGetLastError());
 }
 
 void launch_chol_rinv(hipStream_t st, int w, const double2 *G, double2 *Rinv, int *status,
                       double2 *Rout) {
     if (w < 1 || w > 48) throw Error(-1, "cholqr: width out of range");
-    hipLaunchKernelGGL(chol_rinv_kernel, dim3(1), dim3(256), 0, st, w, G, Rinv, status, Rout, 0,
-                       (double2 *)nullptr, 0);
-    GPLHR_HIP_CHECK(hipGetLastError());
+    launch_chol(st, w, G, Rinv, status, Rout, 0, nullptr, 0);
 }
 
 void launch_chol_proj(hipStream_t st, int wy, int w, const double2 *G, double2 *Rinv, double2 *Cy,
                       int *status, bool guard) {
     if (w < 1 || w > 48 || wy < 0 || wy > 48 || wy + w > 64)
         throw Error(-1, "cholqr: width out of range");
-    hipLaunchKernelGGL(chol_rinv_kernel, dim3(1), dim3(256), 0, st, w, G, Rinv, status,
-                       (double2 *)nullptr, wy, Cy, guard ? 1 : 0);
-    GPLHR_HIP_CHECK(hipGetLastError());
+    launch_chol(st, w, G, Rinv, status, nullptr, wy, Cy, guard ? 1 : 0);
 }
 
 // ---------------------------------------------------------------------------

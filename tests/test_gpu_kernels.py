@@ -450,6 +450,33 @@ def test_proj_orth_matches_qr(device, wy, w, dtype):
         assert np.array_equal(out[:, wy + w:], Z[:, wy + w:])
 
 
+@pytest.mark.parametrize("wy,w", [(0, 1), (7, 1), (0, 15), (1, 17), (31, 31), (31, 33), (17, 47), (48, 15)])
+def test_proj_orth_factor_tiles(device, wy, w):
+    # widths around the factor's 16-column tiles and its largest G_Y, with a
+    # block of condition number 1e3: the first pass's orthogonality loss stays
+    # far below one, so the second leaves n eps, and Q differs from the oracle's
+    # by no more than cond * n eps
+    import torch
+    from oracle.gplhr_oracle import orth
+    from paper_1506_06829_amd import gplhr as G
+    rng = np.random.default_rng(100 * wy + w)
+    n = 300
+    Z = _block(rng, n, wy + w + 1)
+    if wy:
+        Z[:, :wy] = orth(Z[:, :wy])
+    U = np.linalg.qr(rng.standard_normal((w, w)))[0]
+    Z[:, wy:wy + w] = Z[:, wy:wy + w] @ (U * np.logspace(0, -3, w)) @ U.T
+    Y, X = Z[:, :wy], Z[:, wy:wy + w]
+    ref = orth(X - Y @ (Y.conj().T @ X))
+    Zd = torch.as_tensor(Z).to(device)
+    G.proj_orth(Zd, wy, w, passes=2)
+    out = Zd.cpu().numpy()
+    Q = out[:, wy:wy + w]
+    assert np.max(np.abs(Q.conj().T @ Q - np.eye(w))) < n * 2.3e-16
+    assert np.linalg.norm(Q - ref) / np.sqrt(w) < 1e3 * n * 2.3e-16
+    assert np.array_equal(out[:, :wy], Z[:, :wy]) and np.array_equal(out[:, wy + w:], Z[:, wy + w:])
+
+
 @pytest.mark.parametrize("wy", [0, 16])
 def test_proj_orth_reports_rank_deficiency(device, wy):
     # a column that repeats another leaves a vanishing Cholesky pivot:

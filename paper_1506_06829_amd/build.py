@@ -17,7 +17,7 @@ ROOT = PKG.parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libgplhr.so"
 
-SOURCES = ["kernels.hip", "gram_c64.hip", "gram_c128.hip", "gram.hip", "update_c64.hip", "update_c128.hip", "driver.hip", "capi.cpp", "memory.cpp", "small_dense.cpp"]
+SOURCES = ["kernels.hip", "spmm_c64.hip", "spmm_c128.hip", "gram_c64.hip", "gram_c128.hip", "gram.hip", "update_c64.hip", "update_c128.hip", "driver.hip", "capi.cpp", "memory.cpp", "small_dense.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = [

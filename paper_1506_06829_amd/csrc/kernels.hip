@@ -18,318 +18,6 @@
 
 namespace gplhr {
 
-// ---------------------------------------------------------------------------
-// CSR sparse matrix times row-major block
-// ---------------------------------------------------------------------------
-// A group of `lpr` consecutive lanes owns one matrix row; lane l of the group
-// owns CPL consecutive columns of the block (CPL = 2 for complex64 so every
-// lane moves 16 bytes).  The row's index/value stream is read by all lanes of
-// the group at the same address (one broadcast transaction), the gathered
-// block rows are contiguous segments, and no cross-lane reduction is needed.
-
-// CPL consecutive complex values per lane, moved as 16-byte vectors.
-template <typename T, int CPL>
-__device__ __forceinline__ void load_vec(const T *p, T (&x)[CPL]) {
-    if constexpr (sizeof(T) == 16 || CPL == 1) {
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) x[c] = p[c];
-    } else {
-#pragma unroll
-        for (int c = 0; c < CPL; c += 2) {
-            const float4 v = *reinterpret_cast<const float4 *>(p + c);
-            x[c] = make_float2(v.x, v.y);
-            x[c + 1] = make_float2(v.z, v.w);
-        }
-    }
-}
-template <typename T, int CPL>
-__device__ __forceinline__ void store_vec(T *p, const T (&x)[CPL]) {
-    if constexpr (sizeof(T) == 16 || CPL == 1) {
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) p[c] = x[c];
-    } else {
-#pragma unroll
-        for (int c = 0; c < CPL; c += 2)
-            *reinterpret_cast<float4 *>(p + c) = make_float4(x[c].x, x[c].y, x[c + 1].x, x[c + 1].y);
-    }
-}
-// The same with non-temporal stores (streamed past the caches): for outputs
-// too large to stay in the Infinity Cache until they are read again.
-template <typename T, int CPL>
-__device__ __forceinline__ void store_vec_nt(T *p, const T (&x)[CPL]) {
-    typedef float f2n __attribute__((ext_vector_type(2)));
-    typedef float f4n __attribute__((ext_vector_type(4)));
-    typedef double d2n __attribute__((ext_vector_type(2)));
-    if constexpr (sizeof(T) == 16) {
-#pragma unroll
-        for (int c = 0; c < CPL; ++c)
-            __builtin_nontemporal_store(d2n{x[c].x, x[c].y}, reinterpret_cast<d2n *>(p + c));
-    } else if constexpr (CPL == 1) {
-        __builtin_nontemporal_store(f2n{x[0].x, x[0].y}, reinterpret_cast<f2n *>(p));
-    } else {
-#pragma unroll
-        for (int c = 0; c < CPL; c += 2)
-            __builtin_nontemporal_store(f4n{x[c].x, x[c].y, x[c + 1].x, x[c + 1].y},
-                                        reinterpret_cast<f4n *>(p + c));
-    }
-}
-
-template <typename T>
-struct SpmmArgs {
-    int64_t n;
-    const int32_t *rp;
-    const int32_t *ci;
-    const T *val;
-    const T *X;
-    int ldx;
-    T *Y;
-    int ldy;
-    int b;
-    int mode;
-    const T *Rhs;
-    int ldr;
-    const T *dw;
-    int lpr;        // lanes per row
-    int rpw;        // rows per wavefront
-    int nblocks;    // blocks that carry rows
-    int per_xcd;    // >0: XCD-contiguous block remap
-    int sp;         // >0: plane-slab row schedule with planes of sp rows
-    int ss;         // slab: sp / 8 rows of each plane
-    int sperx;      // rows per XCD: n / 8
-    int nt;         // 1: non-temporal stores of Y
-};
-
-// MODE 0: Y = C X; MODE 1: the damped Jacobi sweep Y = X + dw .* (Rhs - C X);
-// MODE 2: the first two sweeps from w_0 = 0 in one pass, Y = w + dw .* (Rhs -
-// C w) with w = dw .* Rhs: X is Rhs and val holds the values of C diag(dw)
-// (launch_scale_cols), so C w is gathered from Rhs directly.  Compile-time, so
-// the plain product carries no epilogue registers.  BATCH entries of a row
-// have their block-row gathers in flight together.
-//
-// Index/value stream through LDS: when the rows of a workgroup are
-// consecutive rows of the matrix (always in natural order; in the plane-slab
-// order unless the workgroup straddles a slab) and their entries fit in
-// SPMM_STAGE entries, the workgroup first copies its row pointers and then
-// its whole contiguous segment of column indices and values into LDS with
-// coalesced loads; each lane group then reads its row's entries from LDS.
-// Otherwise every lane group reads its row's entries from global memory.
-// Both paths take a row's entries in the same order, so the results are the
-// same bit for bit.
-constexpr int SPMM_STAGE = 1024;
-
-template <typename T, int CPL, int MODE, int BATCH>
-__global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
-    __shared__ int32_t s_ci[SPMM_STAGE];
-    __shared__ T s_val[SPMM_STAGE];
-    __shared__ int32_t s_rp[257];
-    int blk = blockIdx.x;
-    if (a.per_xcd > 0) {
-        blk = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
-        if (blk >= a.nblocks) return;
-    }
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int rw = lane / a.lpr;
-    const int cl = lane - rw * a.lpr;
-    auto row_of = [&](int64_t pos) -> int64_t {
-        if (a.sp <= 0) return pos;
-        // XCD x takes slab x of every plane, planes in order (n < 2^31)
-        const int p = (int)pos, x = p / a.sperx, r = p - x * a.sperx, z = r / a.ss;
-        return (int64_t)z * a.sp + (int64_t)x * a.ss + (r - z * a.ss);
-    };
-    // the workgroup's rows: positions pos0 .. pos0 + nr - 1
-    const int rows_blk = 4 * a.rpw;
-    const int64_t pos0 = (int64_t)blk * rows_blk;
-    const int nr = (int)min((int64_t)rows_blk, a.n - pos0);
-    const int64_t row0 = row_of(pos0);
-    const bool contiguous = (row_of(pos0 + nr - 1) - row0 == nr - 1);
-    bool staged = false;
-    int e0 = 0;
-    if (contiguous) {
-        for (int t = threadIdx.x; t <= nr; t += 256) s_rp[t] = a.rp[row0 + t];
-        __syncthreads();
-        e0 = s_rp[0];
-        const int ne = s_rp[nr] - e0;
-        staged = ne <= SPMM_STAGE;   // the same for every thread of the workgroup
-        if (staged) {
-            for (int e = threadIdx.x; e < ne; e += 256) {
-                s_ci[e] = a.ci[e0 + e];
-                s_val[e] = a.val[e0 + e];
-            }
-            __syncthreads();
-        }
-    }
-    const int r = wave * a.rpw + rw;
-    const int c0 = cl * CPL;
-    if (rw >= a.rpw || r >= nr || c0 >= a.b) return;
-    const int64_t row = contiguous ? row0 + r : row_of(pos0 + r);
-
-    // epilogue operands first, so their latency overlaps the gather
-    T xo[CPL], rh[CPL], w = czero<T>();
-    if constexpr (MODE == 1) {
-        load_vec<T, CPL>(a.X + row * a.ldx + c0, xo);
-        load_vec<T, CPL>(a.Rhs + row * a.ldr + c0, rh);
-        w = a.dw[row];
-    } else if constexpr (MODE == 2) {
-        load_vec<T, CPL>(a.Rhs + row * a.ldr + c0, rh);
-        w = a.dw[row];
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) xo[c] = cmul(w, rh[c]);
-    }
-    T acc[CPL];
-#pragma unroll
-    for (int u = 0; u < CPL; ++u) acc[u] = czero<T>();
-    const T *__restrict__ Xc = a.X + c0;
-    // whole batches of the row's index/value stream are in flight before the
-    // dependent block-row gathers are issued
-    auto gather = [&](int j[BATCH], T v[BATCH]) {
-        T x[BATCH][CPL];
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            if (j[u] >= 0) {
-                load_vec<T, CPL>(Xc + (int64_t)j[u] * a.ldx, x[u]);
-            } else {
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) x[u][c] = czero<T>();
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u)
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) cfma(acc[c], v[u], x[u][c]);
-    };
-    if (staged) {
-        const int p0 = s_rp[r] - e0, p1 = s_rp[r + 1] - e0;
-        for (int p = p0; p < p1; p += BATCH) {
-            int j[BATCH];
-            T v[BATCH];
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u) {
-                const bool ok = p + u < p1;
-                j[u] = ok ? s_ci[p + u] : -1;
-                v[u] = ok ? s_val[p + u] : czero<T>();
-            }
-            gather(j, v);
-        }
-    } else {
-        const int p0 = a.rp[row], p1 = a.rp[row + 1];
-        for (int p = p0; p < p1; p += BATCH) {
-            int j[BATCH];
-            T v[BATCH];
-#pragma unroll
-            for (int u = 0; u < BATCH; ++u) {
-                const bool ok = p + u < p1;
-                j[u] = ok ? a.ci[p + u] : -1;
-                v[u] = ok ? a.val[p + u] : czero<T>();
-            }
-            gather(j, v);
-        }
-    }
-    T out[CPL];
-    if constexpr (MODE == 0) {
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) out[c] = acc[c];
-    } else {
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) {
-            out[c] = xo[c];
-            cfma(out[c], w, csub(rh[c], acc[c]));
-        }
-    }
-    if (a.nt) store_vec_nt<T, CPL>(a.Y + row * a.ldy + c0, out);
-    else store_vec<T, CPL>(a.Y + row * a.ldy + c0, out);
-}
-
-// Row schedule.  Without a plane, rows run in natural order and blocks are
-// dealt to the XCDs round robin, so the block rows a row gathers (its
-// neighbours one plane away, for a PDE operator in natural ordering) are
-// fetched into several XCDs' L2.  With a plane of P rows (all couplings
-// within +-P rows, n a multiple of P, P a multiple of 8), blocks are remapped
-// so that XCD x runs slab x (rows x P/8 ... (x+1) P/8 - 1) of every plane,
-// plane after plane: the three planes of one slab that a block touches fit
-// in that XCD's L2, and every block row is fetched about once (160^3 operator,
-// 16 complex64 columns: 1.96 -> 0.93 GB read per product).
-//
-// Batch length.  A row's entries are taken BATCH at a time: their indices and
-// values first, then all their block-row gathers, so a row of at most BATCH
-// entries costs one round of dependent latencies.  BATCH follows the typical
-// row length (nnz / n): 8, 12 or 17 slots.  17 is the most the complex128
-// kernel with two columns per lane keeps within 256 VGPRs (225, two waves per
-// SIMD); 20 slots overflow into AGPRs at one wave per SIMD and run slower.
-// Measured at n = 262144, 17 random entries per row, 10 complex128 columns:
-// 176 us with 8 slots, 166 us with 12, 153 us with 17; the 7-point 160^3
-// operator (16 complex64 columns) keeps 8 (431 us; 17 slots: 564 us).
-template <typename T, int MODE, int BATCH>
-static void spmm_go(hipStream_t st, const SpmmArgs<T> &a, int cpl, int grid) {
-    if (cpl == 2)
-        hipLaunchKernelGGL((spmm_kernel<T, 2, MODE, BATCH>), dim3(grid), dim3(256), 0, st, a);
-    else
-        hipLaunchKernelGGL((spmm_kernel<T, 1, MODE, BATCH>), dim3(grid), dim3(256), 0, st, a);
-}
-
-template <typename T, int MODE>
-static void spmm_batch(hipStream_t st, const SpmmArgs<T> &a, int cpl, int grid, int row_len) {
-    if (row_len <= 8) spmm_go<T, MODE, 8>(st, a, cpl, grid);
-    else if (row_len <= 12) spmm_go<T, MODE, 12>(st, a, cpl, grid);
-    else spmm_go<T, MODE, 17>(st, a, cpl, grid);
-}
-
-template <typename T>
-void launch_spmm(hipStream_t st, int64_t n, const int32_t *rp, const int32_t *ci, const T *val,
-                 const T *X, int ldx, T *Y, int ldy, int b, int mode, const T *Rhs, int ldr,
-                 const T *dw, int plane, int64_t nnz) {
-    if (n <= 0) return;
-    if (plane < 0 || (plane > 0 && (n % plane != 0 || plane % 8 != 0)))
-        throw Error(-1, "spmm: the plane must divide n and be a multiple of 8");
-    SpmmArgs<T> a{n, rp, ci, val, X, ldx, Y, ldy, b, mode, Rhs, ldr, dw, 0, 0, 0, 0, 0, 0, 0, 0};
-    // an output block larger than the 256 MB Infinity Cache cannot stay there
-    // until it is read again: stream it past the caches
-    a.nt = ((double)n * b * sizeof(T) > 256.0 * 1024 * 1024) ? 1 : 0;
-    // lanes move two complex values of the block row: 16 bytes (complex64)
-    // or 32 bytes (complex128).  For complex64 this beat four values (32
-    // bytes) per lane on the 160^3 operator with 16 columns, 380 -> 345 us
-    // (product), 446 -> 425 us and 527 -> 506 us (the Jacobi epilogues), at the
-    // same results: twice the lanes per row, at fewer registers per lane.
-    const uintptr_t align = reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y) |
-                            (mode != 0 ? reinterpret_cast<uintptr_t>(Rhs) : 0);
-    int cpl = 1;
-    if constexpr (sizeof(T) == 8) {
-        const bool ok2 = (b % 2 == 0) && (ldx % 2 == 0) && (ldy % 2 == 0) &&
-                         (mode == 0 || ldr % 2 == 0) && align % 16 == 0;
-        cpl = ok2 ? 2 : 1;
-    } else {
-        cpl = (b % 2 == 0) ? 2 : 1;
-    }
-    a.lpr = (b + cpl - 1) / cpl;
-    if (a.lpr > 64) throw Error(-1, "spmm: block too wide");
-    a.rpw = 64 / a.lpr;
-    const int64_t rows_per_block = 4LL * a.rpw;
-    const int nblocks = ceil_div_i(n, rows_per_block);
-    a.nblocks = nblocks;
-    int grid = nblocks;
-    if (plane > 0) {
-        grid = (nblocks + 7) / 8 * 8;
-        a.per_xcd = grid / 8;
-        a.sp = plane;
-        a.ss = plane / 8;
-        a.sperx = (int)(n / 8);
-    }
-    // typical entries per row, rounded up
-    const int64_t row_len = nnz > 0 ? (nnz + n - 1) / n : 0;
-    const int rl = (int)std::min<int64_t>(row_len, 1 << 20);
-    if (mode == 0) spmm_batch<T, 0>(st, a, cpl, grid, rl);
-    else if (mode == 1) spmm_batch<T, 1>(st, a, cpl, grid, rl);
-    else spmm_batch<T, 2>(st, a, cpl, grid, rl);
-    GPLHR_HIP_CHECK(hipGetLastError());
-}
-
-template void launch_spmm<double2>(hipStream_t, int64_t, const int32_t *, const int32_t *,
-                                   const double2 *, const double2 *, int, double2 *, int, int,
-                                   int, const double2 *, int, const double2 *, int, int64_t);
-template void launch_spmm<float2>(hipStream_t, int64_t, const int32_t *, const int32_t *,
-                                  const float2 *, const float2 *, int, float2 *, int, int, int,
-                                  const float2 *, int, const float2 *, int, int64_t);
-
 // Largest |j - i| over the stored entries (columns sorted within each row:
 // the first and the last entry of a row bound it).
 __global__ void bandwidth_kernel(int64_t n, const int32_t *rp, const int32_t *ci,

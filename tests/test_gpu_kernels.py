@@ -171,6 +171,56 @@ def test_csr_plane_of_unstructured_patterns(device):
         G.spmm(A, X, plane=24)
 
 
+@pytest.mark.parametrize("b", [1, 2, 5, 16, 33, 64])
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("lengths", [(5,), (7,), (0, 3, 12), (17,), (0, 0, 130, 1), (40, 300, 2)])
+def test_spmm_row_lengths(device, b, dtype, lengths):
+    # rows that fill a batch of gathers, fall short of it or run past it, empty
+    # rows, and wavefronts whose entries do and do not fit their stage; block
+    # rows that no entry refers to hold NaN.  A row of L entries sums L products:
+    # (L + 2) eps of the sum of moduli.
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    rng = np.random.default_rng(b + sum(lengths))
+    n = 1031
+    cnt = np.array([lengths[i % len(lengths)] for i in range(n)])
+    ip = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int32)
+    ci = rng.integers(0, n - 7, ip[-1]).astype(np.int32)
+    ci = np.concatenate([np.sort(ci[ip[i]:ip[i + 1]]) for i in range(n)]).astype(np.int32)
+    val = rng.standard_normal(ip[-1]) + 1j * rng.standard_normal(ip[-1])
+    X = _block(rng, n, b)
+    if dtype == "c64":
+        val, X = (z.astype(np.complex64).astype(np.complex128) for z in (val, X))
+    A = sp.csr_matrix((val, ci, ip), shape=(n, n))
+    ref = A @ X
+    scale = abs(A) @ np.abs(X)
+    X[n - 7:] = np.nan
+    tdt = torch.complex128 if dtype == "c128" else torch.complex64
+    dA = G.DeviceCsr(n, torch.as_tensor(ip).to(device), torch.as_tensor(ci).to(device),
+                     torch.as_tensor(val).to(device))
+    ld = b + (b % 3)
+    Xd = torch.zeros((n, ld), dtype=tdt, device=device)
+    Xd[:, :b] = torch.as_tensor(X).to(device, tdt)
+    Y = G.spmm(dA, Xd[:, :b], val=dA.val.to(tdt)).cpu().numpy().astype(np.complex128)
+    eps = 2.3e-16 if dtype == "c128" else 1.2e-7
+    assert np.all(np.abs(Y - ref) <= 4 * (max(lengths) + 2) * eps * scale)
+
+
+def test_spmm_of_rows_far_apart(device):
+    # a block that spans more than 32-bit byte offsets
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    rng = np.random.default_rng(4)
+    n, ld, b = 40, 7_000_000, 6
+    A = sp.random(n, n, density=0.3, random_state=5, format="csr") + sp.identity(n, format="csr")
+    dA = G.DeviceCsr.from_host(problems.csr_from_scipy(A))
+    x = _block(rng, n, b)
+    X = torch.zeros((n - 1) * ld + b, dtype=torch.complex128, device=device).as_strided((n, b), (ld, 1))
+    X.copy_(torch.as_tensor(x))
+    Y = G.spmm(dA, X).cpu().numpy()
+    assert np.all(np.abs(Y - A @ x) <= 4 * (n + 2) * 2.3e-16 * (abs(A) @ np.abs(x)))
+
+
 @pytest.mark.parametrize("bx,by", [(1, 1), (5, 10), (10, 10), (16, 16), (30, 48), (48, 48), (64, 64),
                                    (40, 40), (40, 30), (40, 24), (33, 37)])
 @pytest.mark.parametrize("dtype", ["c128", "c64"])

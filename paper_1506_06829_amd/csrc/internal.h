@@ -43,11 +43,18 @@ void pinned_free(void *p, size_t bytes);
 // in the plane-slab order (plane rows per plane; must divide n and be a
 // multiple of 8), 0 in natural order; the result is the same.  nnz (the
 // stored entries, rp[n]) sets how many entries of a row are gathered at once;
-// any value >= 0 gives the same result.
+// any value >= 0 gives the same result.  Y is left as it was where stop is not
+// null and holds a nonzero count.
 template <typename T>
 void launch_spmm(hipStream_t st, int64_t n, const int32_t *rp, const int32_t *ci, const T *val,
                  const T *X, int ldx, T *Y, int ldy, int b, int mode, const T *Rhs, int ldr,
-                 const T *dw, int plane, int64_t nnz);
+                 const T *dw, int plane, int64_t nnz, const unsigned long long *stop = nullptr);
+// Mode 2 with the values of C diag(dw) formed on the way from C's complex128
+// values; dwT: dw in the block's type.  The same result.
+template <typename T>
+void launch_jacobi2(hipStream_t st, int64_t n, const int32_t *rp, const int32_t *ci, const double2 *val,
+                    const double2 *dw, const T *dwT, const T *R, int ldr, T *Y, int ldy, int b, int plane,
+                    int64_t nnz, const unsigned long long *stop);
 // Plane for launch_spmm: the pattern's bandwidth max |j - i| when it splits
 // n into at least four planes of at least 512 rows (a multiple of 8), else 0.
 // Synchronous.
@@ -167,6 +174,10 @@ int64_t extract_diag(hipStream_t st, int64_t n, const int32_t *rp, const int32_t
                      const double2 *val, double2 *d);
 // out[i] = num / d[i]
 void launch_recip_scaled(hipStream_t st, int64_t n, const double2 *d, double2 num, double2 *out);
+// dw[i] = omega / C(i,i), also rounded to complex64 into dw32 unless it is null;
+// adds the number of zero (or not stored) diagonal entries to *zeros.
+void launch_jacobi_scale(hipStream_t st, int64_t n, const int32_t *rp, const int32_t *ci, const double2 *val,
+                         double omega, double2 *dw, float2 *dw32, unsigned long long *zeros);
 // Values of C diag(s) on C's pattern: out[e] = val[e] * s[ci[e]] (one rounding
 // per entry), for the two-sweep Jacobi product (launch_spmm mode 2).
 void launch_scale_cols(hipStream_t st, int64_t nnz, const int32_t *ci, const double2 *val,

@@ -1313,24 +1313,26 @@ int64_t build_shifted(hipStream_t st, int64_t n, int64_t anz, const int32_t *arp
     return nnz;
 }
 
-__global__ void diag_kernel(int64_t n, const int32_t *rp, const int32_t *ci, const double2 *val,
-                            double2 *d, unsigned long long *zeros) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+// C(i,i), or zero where it is not stored (columns sorted within the row).
+__device__ __forceinline__ double2 diag_entry(int64_t i, const int32_t *rp, const int32_t *ci,
+                                              const double2 *val) {
     int lo = rp[i], hi = rp[i + 1] - 1;
-    double2 v = make_double2(0.0, 0.0);
     while (lo <= hi) {
         const int mid = (lo + hi) >> 1;
         const int c = ci[mid];
-        if (c == i) {
-            v = val[mid];
-            break;
-        }
+        if (c == i) return val[mid];
         if (c < i)
             lo = mid + 1;
         else
             hi = mid - 1;
     }
+    return make_double2(0.0, 0.0);
+}
+__global__ void diag_kernel(int64_t n, const int32_t *rp, const int32_t *ci, const double2 *val,
+                            double2 *d, unsigned long long *zeros) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const double2 v = diag_entry(i, rp, ci, val);
     d[i] = v;
     if (v.x == 0.0 && v.y == 0.0) atomicAdd(zeros, 1ULL);
 }
@@ -1349,14 +1351,30 @@ int64_t extract_diag(hipStream_t st, int64_t n, const int32_t *rp, const int32_t
     return (int64_t)h;
 }
 
+// num / v = num * conj(v) / |v|^2
+__device__ __forceinline__ double2 quotient(double2 num, double2 v) {
+    const double den = v.x * v.x + v.y * v.y;
+    return make_double2((num.x * v.x + num.y * v.y) / den, (num.y * v.x - num.x * v.y) / den);
+}
 __global__ void recip_kernel(int64_t n, const double2 *d, double2 num, double2 *out) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) out[i] = quotient(num, d[i]);
+}
+__global__ void jacobi_scale_kernel(int64_t n, const int32_t *rp, const int32_t *ci, const double2 *val,
+                                    double omega, double2 *dw, float2 *dw32, unsigned long long *zeros) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const double2 v = d[i];
-    const double den = v.x * v.x + v.y * v.y;
-    // num / v = num * conj(v) / |v|^2
-    const double2 q = make_double2((num.x * v.x + num.y * v.y) / den, (num.y * v.x - num.x * v.y) / den);
-    out[i] = q;
+    const double2 v = diag_entry(i, rp, ci, val);
+    if (v.x == 0.0 && v.y == 0.0) atomicAdd(zeros, 1ULL);
+    const double2 q = quotient(make_double2(omega, 0.0), v);
+    dw[i] = q;
+    if (dw32) dw32[i] = from_d<float2>(q);
+}
+void launch_jacobi_scale(hipStream_t st, int64_t n, const int32_t *rp, const int32_t *ci, const double2 *val,
+                         double omega, double2 *dw, float2 *dw32, unsigned long long *zeros) {
+    hipLaunchKernelGGL(jacobi_scale_kernel, dim3(ceil_div_i(n, 256)), dim3(256), 0, st, n, rp, ci, val, omega,
+                       dw, dw32, zeros);
+    GPLHR_HIP_CHECK(hipGetLastError());
 }
 void launch_recip_scaled(hipStream_t st, int64_t n, const double2 *d, double2 num, double2 *out) {
     hipLaunchKernelGGL(recip_kernel, dim3(ceil_div_i(n, 256)), dim3(256), 0, st, n, d, num, out);

@@ -75,6 +75,8 @@ struct SpmmArgs {
     const T *Rhs;
     int ldr;
     const T *dw;
+    const double2 *dval, *dcs;        // MODE 3: C's values and dw
+    const unsigned long long *stop;   // not null and not zero: leave Y alone
     int lpr;        // lanes per row
     int inv;        // ceil(65536 / lpr): lane / lpr as a multiplication
     int rpw;        // rows per wavefront
@@ -88,8 +90,10 @@ struct SpmmArgs {
 // MODE 0: Y = C X; MODE 1: the damped Jacobi sweep Y = X + dw .* (Rhs - C X);
 // MODE 2: the first two sweeps from w_0 = 0 in one pass, Y = w + dw .* (Rhs -
 // C w) with w = dw .* Rhs: X is Rhs and val holds the values of C diag(dw)
-// (launch_scale_cols), so C w is gathered from Rhs directly.  Compile-time, so
-// the plain product carries no epilogue registers.  BATCH entries of a row
+// (launch_scale_cols), so C w is gathered from Rhs directly; MODE 3: the same
+// with the values formed while they are staged (rounded as launch_scale_cols and
+// a conversion to complex64 do).  Compile-time, so the plain product carries no
+// epilogue registers.  BATCH entries of a row
 // have their block-row gathers in flight together.
 //
 // Index/value stream through LDS: where the entries of a wavefront's rows (always
@@ -123,6 +127,11 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
     __shared__ T s_val[4 * WS];
     __shared__ int32_t s_rp[260];
     const int tid = threadIdx.x, lane = tid & 63;
+    if (a.stop && *a.stop) return;
+    auto value_of = [&](int e, int32_t j) {
+        if constexpr (MODE == 3) return from_d<T>(cmul(a.dval[e], a.dcs[j]));
+        else return a.val[e];
+    };
     // the workgroup's rows: row0 .. row0 + nr - 1
     int64_t row0;
     int nr;
@@ -159,8 +168,15 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
             if (64 * q < ne) {   // entries past the last repeat it
                 const int e = e0 + min(64 * q + lane, ne - 1);
                 ci[q] = a.ci[e];
-                val[q] = reinterpret_cast<const vec *>(a.val)[e];
+                if constexpr (MODE != 3) val[q] = reinterpret_cast<const vec *>(a.val)[e];
             }
+        if constexpr (MODE == 3)
+#pragma unroll
+            for (int q = 0; q < WS / 64; ++q)
+                if (64 * q < ne) {
+                    const T f = value_of(e0 + min(64 * q + lane, ne - 1), ci[q]);
+                    val[q] = vec{f.x, f.y};
+                }
         if (lane < nr) w_rp[lane] = rp - e0;
         if (lane == 0) w_rp[nr] = ne;
 #pragma unroll
@@ -183,7 +199,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
         load_vec<T, CPL>(a.X + row * a.ldx + c0, xo);
         load_vec<T, CPL>(a.Rhs + row * a.ldr + c0, rh);
         w = a.dw[row];
-    } else if constexpr (MODE == 2) {
+    } else if constexpr (MODE >= 2) {
         load_vec<T, CPL>(a.Rhs + row * a.ldr + c0, rh);
         w = a.dw[row];
 #pragma unroll
@@ -241,7 +257,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
     else
         walk(a.rp[row], a.rp[row + 1],
              [&](int e) { return S32 ? (uint32_t)a.ci[e] * rowb : (uint32_t)a.ci[e]; },
-             [&](int e) { return a.val[e]; }, std::false_type{});
+             [&](int e) { return value_of(e, MODE == 3 ? a.ci[e] : 0); }, std::false_type{});
     T out[CPL];
     if constexpr (MODE == 0) {
 #pragma unroll
@@ -292,15 +308,12 @@ static void spmm_batch(hipStream_t st, const SpmmArgs<T> &a, int cpl, int grid, 
 }
 
 template <typename T>
-void launch_spmm(hipStream_t st, int64_t n, const int32_t *rp, const int32_t *ci, const T *val,
-                 const T *X, int ldx, T *Y, int ldy, int b, int mode, const T *Rhs, int ldr,
-                 const T *dw, int plane, int64_t nnz) {
+static void spmm_launch(hipStream_t st, SpmmArgs<T> a, int mode, int plane, int64_t nnz) {
+    const int64_t n = a.n;
+    const int b = a.b;
     if (n <= 0) return;
     if (plane < 0 || (plane > 0 && (n % plane != 0 || plane % 8 != 0)))
         throw Error(-1, "spmm: the plane must divide n and be a multiple of 8");
-    SpmmArgs<T> a{};
-    a.n = n; a.rp = rp; a.ci = ci; a.val = val; a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy; a.b = b;
-    a.Rhs = Rhs; a.ldr = ldr; a.dw = dw;
     // an output block larger than the 256 MB Infinity Cache cannot stay there
     // until it is read again: stream it past the caches
     a.nt = ((double)n * b * sizeof(T) > 256.0 * 1024 * 1024) ? 1 : 0;
@@ -313,12 +326,12 @@ void launch_spmm(hipStream_t st, int64_t n, const int32_t *rp, const int32_t *ci
     // (262144 rows of 17 random entries, 10 columns: 151 us against 154; longer rows
     // want the wavefronts in flight, 60000 rows of 40: 59 against 56.5, up to wide
     // blocks: with 32 columns 150 against 155).
-    const uintptr_t align = reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y) |
-                            (mode != 0 ? reinterpret_cast<uintptr_t>(Rhs) : 0);
+    const uintptr_t align = reinterpret_cast<uintptr_t>(a.X) | reinterpret_cast<uintptr_t>(a.Y) |
+                            (mode != 0 ? reinterpret_cast<uintptr_t>(a.Rhs) : 0);
     int cpl = 1;
     if constexpr (sizeof(T) == 8) {
-        const bool ok2 = (b % 2 == 0) && (ldx % 2 == 0) && (ldy % 2 == 0) &&
-                         (mode == 0 || ldr % 2 == 0) && align % 16 == 0;
+        const bool ok2 = (b % 2 == 0) && (a.ldx % 2 == 0) && (a.ldy % 2 == 0) &&
+                         (mode == 0 || a.ldr % 2 == 0) && align % 16 == 0;
         cpl = ok2 ? 2 : 1;
     } else if (b > 64 || (row_len > 12 && (row_len <= 17 || b > 16) && n * b >= (1 << 20))) {
         cpl = b % 2 == 0 ? 2 : 1;
@@ -346,8 +359,29 @@ void launch_spmm(hipStream_t st, int64_t n, const int32_t *rp, const int32_t *ci
     const int rl = (int)std::min<int64_t>(row_len, 1 << 20);
     if (mode == 0) spmm_batch<T, 0>(st, a, cpl, (int)grid, rl);
     else if (mode == 1) spmm_batch<T, 1>(st, a, cpl, (int)grid, rl);
-    else spmm_batch<T, 2>(st, a, cpl, (int)grid, rl);
+    else if (mode == 2) spmm_batch<T, 2>(st, a, cpl, (int)grid, rl);
+    else spmm_batch<T, 3>(st, a, cpl, (int)grid, rl);
     GPLHR_HIP_CHECK(hipGetLastError());
+}
+
+template <typename T>
+void launch_spmm(hipStream_t st, int64_t n, const int32_t *rp, const int32_t *ci, const T *val,
+                 const T *X, int ldx, T *Y, int ldy, int b, int mode, const T *Rhs, int ldr,
+                 const T *dw, int plane, int64_t nnz, const unsigned long long *stop) {
+    SpmmArgs<T> a{};
+    a.n = n; a.rp = rp; a.ci = ci; a.val = val; a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy; a.b = b;
+    a.Rhs = Rhs; a.ldr = ldr; a.dw = dw; a.stop = stop;
+    spmm_launch<T>(st, a, mode, plane, nnz);
+}
+
+template <typename T>
+void launch_jacobi2(hipStream_t st, int64_t n, const int32_t *rp, const int32_t *ci, const double2 *val,
+                    const double2 *dw, const T *dwT, const T *R, int ldr, T *Y, int ldy, int b, int plane,
+                    int64_t nnz, const unsigned long long *stop) {
+    SpmmArgs<T> a{};
+    a.n = n; a.rp = rp; a.ci = ci; a.X = R; a.ldx = ldr; a.Y = Y; a.ldy = ldy; a.b = b;
+    a.Rhs = R; a.ldr = ldr; a.dw = dwT; a.dval = val; a.dcs = dw; a.stop = stop;
+    spmm_launch<T>(st, a, 3, plane, nnz);
 }
 
 }  // namespace gplhr

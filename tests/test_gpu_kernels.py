@@ -171,6 +171,24 @@ def test_csr_plane_of_unstructured_patterns(device):
         G.spmm(A, X, plane=24)
 
 
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("sweeps", [1, 2, 3, 5])
+def test_jacobi_zero_diagonal_leaves_output(device, dtype, sweeps):
+    # the zero is found on the device: no sweep may write Y before the error
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    C = sp.random(300, 300, density=0.02, random_state=3, format="lil").astype(complex)
+    C.setdiag(4.0)
+    C[77, 77] = 0.0
+    A = G.DeviceCsr.from_host(problems.csr_from_scipy(sp.csr_matrix(C)))
+    tdt = torch.complex128 if dtype == "c128" else torch.complex64
+    R = torch.ones((300, 6), dtype=tdt, device=device)
+    Y = torch.full((300, 6), 7.0, dtype=tdt, device=device)
+    rc = G.lib().gplhr_jacobi(0 if dtype == "c128" else 1, A.n, A.nnz, G._ptr(A.row_ptr), G._ptr(A.col_idx),
+                              G._ptr(A.val), 0.7, sweeps, G._ptr(R), 6, G._ptr(Y), 6, 6, 0, G._stream_ptr())
+    assert rc == -1 and bool((Y == 7.0).all())
+
+
 @pytest.mark.parametrize("b", [1, 2, 5, 16, 33, 64])
 @pytest.mark.parametrize("dtype", ["c128", "c64"])
 @pytest.mark.parametrize("lengths", [(5,), (7,), (0, 3, 12), (17,), (0, 0, 130, 1), (40, 300, 2)])

@@ -31,7 +31,7 @@ COMMON = [
 # back around every MFMA loop: a register-only FP64 MFMA loop ran at 36 TFLOP/s
 # in that form and at 77 in this one.
 MFMA_VGPR = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-EXTRA = {f: MFMA_VGPR for f in ("gram_c64.hip", "gram_c128.hip", "update_c64.hip", "update_c128.hip")}
+EXTRA = {f: MFMA_VGPR for f in ("gram_c64.hip", "gram_c128.hip", "gram.hip", "update_c64.hip", "update_c128.hip")}
 # -fcx-limited-range: textbook complex multiply/divide (no NaN/Inf recovery
 # calls); the small dense step never sees magnitudes near the overflow range
 HOST_ONLY = ["-O3", "-std=c++17", "-fPIC", "-march=x86-64-v3", "-fcx-limited-range", f"-I{CSRC}"]

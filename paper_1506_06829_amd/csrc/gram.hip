@@ -2,6 +2,7 @@
 #include "gram.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace gplhr {
 
@@ -24,6 +25,94 @@ __global__ __launch_bounds__(256) void gram_strided_kernel(GramArgs<T> a) {
         __syncthreads();
     }
     if (threadIdx.x == 0) a.out[p + (int64_t)q * a.ldo] = sh[0];
+}
+
+// One workgroup per tile over all rows, for blocks of few rows: no partials and
+// no second kernel.  Wavefront w takes the K steps (4 rows) w, w + 16, ..., up to
+// PF of them in flight, and the wavefronts' tiles are summed in that order; a
+// tile's sum does not depend on the other columns.
+//
+// What bounds it: the launch, two dependent latencies (operands, LDS) and one
+// CU's matrix rate per tile (4 cycles a row).  Against the kernels with partials
+// (us, parts / tile): 64 rows 5.9 / 3.5, 64 x 64 10.0 / 3.8; 1024 rows, complex128
+// 16 x 16 6.3 / 6.0, 64 x 64 11.8 / 6.2, complex64 16 x 16 6.3 / 5.2; 2048 rows,
+// complex128 16 x 16 6.8 / 9.4, 64 x 64 14.1 / 9.8.  Hence: up to 1024 rows, and up
+// to 2048 where there are more than 16 tiles.
+template <typename T>
+__global__ __launch_bounds__(1024) void gram_tile_kernel(GramArgs<T> a) {
+    using R = typename RealOf<T>::R;
+    constexpr int PF = 8;
+    __shared__ double red[16][256];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int li = lane & 15, lk = lane >> 4;
+    int i = blockIdx.x, j = 0;
+    if (a.tri) {
+        while (i >= a.ma1 + j + 1) { i -= a.ma1 + j + 1; ++j; }
+    } else {
+        j = i / a.ma;
+        i -= j * a.ma;
+    }
+    // A's and B's unit: first column and columns left from there on (TRI: X holds
+    // wy columns, then w; B's units are those of w)
+    const int wy = a.bx - a.by;
+    const bool two = a.Y2 && j >= a.mb1;
+    const int xc = a.tri ? (i < a.ma1 ? i * 8 : wy + (i - a.ma1) * 8) : i * 8;
+    const int xw = (a.tri && i < a.ma1 ? wy : a.bx) - xc;
+    const int yc = a.tri ? wy + j * 8 : (two ? j - a.mb1 : j) * 8;
+    const int yw = (a.tri ? a.bx : a.Y2 ? (two ? a.by - a.by1 : a.by1) : a.by) - yc;
+    const T *Y = a.tri ? a.X : two ? a.Y2 : a.Y;
+    const int ldy = a.tri ? a.ldx : two ? a.ldy2 : a.ldy;
+    const T *sc = a.yscale && (!a.Y2 || two) ? a.yscale : nullptr;
+    auto offs = [&](int ld, int w, int k) {   // bytes; columns past the block repeat its last one
+        return (uint32_t)((k * (int64_t)ld) * sizeof(T) + min(li, 2 * w - 2 + (li & 1)) * sizeof(R));
+    };
+    const uint32_t oa = offs(a.ldx, xw, lk), ob = offs(ldy, yw, lk), os = lk * (uint32_t)sizeof(T);
+    d4v acc = d4v{0.0, 0.0, 0.0, 0.0};
+    // PF K steps from row r0 on; rows past the end (not `full`) read the last row
+    // and enter as zeros
+    auto steps = [&](int r0, auto full, auto scaled) {
+        constexpr bool FULL = decltype(full)::value, SC = decltype(scaled)::value;
+        R va[PF], vb[PF];
+        T vs[PF];
+#pragma unroll
+        for (int p = 0; p < PF; ++p) {
+            const int r = FULL ? r0 + 64 * p : min(r0 + 64 * p, (int)a.n - 1);
+            const int back = FULL ? 0 : max(r + lk - ((int)a.n - 1), 0);   // rows past the end, this lane
+            const char *px = reinterpret_cast<const char *>(a.X + xc + (int64_t)r * a.ldx);
+            const char *py = reinterpret_cast<const char *>(Y + yc + (int64_t)r * ldy);
+            va[p] = *reinterpret_cast<const R *>(px + (FULL ? oa : offs(a.ldx, xw, lk - back)));
+            vb[p] = *reinterpret_cast<const R *>(py + (FULL ? ob : offs(ldy, yw, lk - back)));
+            if constexpr (SC) vs[p] = *reinterpret_cast<const T *>(reinterpret_cast<const char *>(sc + r) + os -
+                                                                   back * sizeof(T));
+        }
+#pragma unroll
+        for (int p = 0; p < PF; ++p) {
+            if (!FULL && r0 + 64 * p >= a.n) break;
+            const bool ok = FULL || r0 + 64 * p + lk < a.n;
+            double y = (double)vb[p];
+            if constexpr (SC) {
+                const double2 f = to_d(vs[p]);
+                y = f.x * y + ((li & 1) ? f.y : -f.y) * (double)other_part(vb[p]);
+            }
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ok ? (double)va[p] : 0.0, ok ? y : 0.0, acc, 0, 0, 0);
+        }
+    };
+    auto rows = [&](auto scaled) {
+        int r0 = 4 * wave;
+        for (; r0 + 64 * (PF - 1) + 4 <= a.n; r0 += 64 * PF) steps(r0, std::true_type{}, scaled);
+        if (r0 < a.n) steps(r0, std::false_type{}, scaled);
+    };
+    if (sc) rows(std::true_type{});
+    else rows(std::false_type{});
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[wave][v * 64 + lane] = acc[v];
+    __syncthreads();
+    if (wave < 4) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) s += red[w][threadIdx.x];
+        gram_put_rows(a, blockIdx.x, wave, s);
+    }
 }
 
 size_t gram_part_entries(int bx, int by) {
@@ -73,6 +162,14 @@ static void launch_gram_impl(hipStream_t st, int64_t n, const T *X, int ldx, int
     }
     if (!fn) throw Error(-1, "gram: no tile layout for this shape");
     a.ntile = gram_tiles(a.ma, a.mb, a.ma1, a.tri);
+    // X^H X takes the path of X^H Y of its width, so that the same block passed as
+    // a copy gives the same bits
+    const int tiles = a.tri && a.ma1 == 0 ? a.ma * a.mb : a.ntile;
+    if (n <= 1024 || (n <= 2048 && tiles > 16)) {
+        hipLaunchKernelGGL(gram_tile_kernel<T>, dim3(a.ntile), dim3(1024), 0, st, a);
+        GPLHR_HIP_CHECK(hipGetLastError());
+        return;
+    }
     const int ks = 4 / gram_groups(a.ma, a.mb, a.ma1, a.tri);
     // Row blocks: one per 32 rows while that leaves CUs idle (a wave then has
     // two K steps, both in flight at once; 1024 rows, complex128, 32 x 32: 8.7 us
@@ -82,8 +179,7 @@ static void launch_gram_impl(hipStream_t st, int64_t n, const T *X, int ldx, int
     // 14 x 14 20.1 us with 1024 blocks and 15.1 with 256, 40 x 40 91 us with 256
     // and 75 with 512; 4096000 rows, complex64, 16 x 16 118 us with 1024 blocks
     // and 141 with 256; 20000 rows, 10 x 10 9.9 us with 256 blocks, 7.5 with 156.
-    // (X^H X as X^H Y of its width, see gram_groups.)
-    const bool wide = (a.tri && a.ma1 == 0 ? a.ma * a.mb : a.ntile) > 8;
+    const bool wide = tiles > 8;
     int64_t nblk = std::max({std::min<int64_t>(128, n / 32), std::min<int64_t>(256, n / 128),
                              std::min<int64_t>(wide ? 512 : 1024, n / (wide ? 512 : 1024)), (int64_t)1});
     nblk = std::min<int64_t>(nblk, (int64_t)(part_cap / (128 * (size_t)a.ntile)));

@@ -344,6 +344,26 @@ def test_gram_of_odd_unit_counts(device, bx, by, dtype):
         assert np.max(np.abs(Gm - X.conj().T @ Y) / scale) < 4 * (n + 4) * 2.3e-16, n
 
 
+@pytest.mark.parametrize("bx,by,own", [(17, 9, False), (9, 17, False), (64, 64, False), (40, 16, True), (20, 20, True)])
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_gram_of_few_rows(device, bx, by, own, dtype):
+    # one workgroup per tile over all rows: row counts around a wavefront's steps
+    # and around the sizes at which the kernels with partials take over.  Bound
+    # as above: n products per entry.
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    tdt = torch.complex128 if dtype == "c128" else torch.complex64
+    g = torch.Generator(device="cpu").manual_seed(bx * 100 + by)
+    for n in (2, 61, 64, 449, 452, 513, 963, 1024, 1025, 2047, 2048, 2049):
+        Xd = torch.randn(n, bx, dtype=tdt, generator=g).to(device)
+        Yd = Xd[:, bx - by:] if own else torch.randn(n, by, dtype=tdt, generator=g).to(device)
+        Gm = G.gram(Xd, Yd).cpu().numpy()
+        X, Y = Xd.cpu().numpy().astype(np.complex128), Yd.cpu().numpy().astype(np.complex128)
+        scale = np.abs(X).T @ np.abs(Y)
+        assert np.max(np.abs(Gm - X.conj().T @ Y) / scale) < 4 * (n + 4) * 2.3e-16, n
+        assert np.array_equal(Gm, G.gram(Xd, Yd.clone() if own and bx == by else Yd).cpu().numpy()), n
+
+
 def test_gram_of_rows_far_apart(device):
     # a leading dimension whose rows lie further apart than the kernels' 32-bit
     # offsets reach

@@ -360,11 +360,12 @@ def test_converged_parity_block_shapes(device, k, block, locking):
     assert match_err(lam[:k], ref.lam[:k]) < 1e-10
 
 
-@pytest.mark.parametrize("block", [13, 14])
-def test_converged_parity_of_a_wide_trial_space(device, block):
+@pytest.mark.parametrize("n,block", [(3000, 13), (3000, 14), (900, 6), (901, 14)])
+def test_converged_parity_of_a_wide_trial_space(device, n, block):
     # 52 and 56 trial columns and a diagonal B: the projected pencil's Gram
-    # takes the row scale with seven 8-column units
-    p = problems.config("d1", 3000)
+    # takes the row scale with seven 8-column units; and on few rows, where one
+    # workgroup forms each of its tiles
+    p = problems.config("d1", n)
     p.k, p.block = 5, block
     p.V0 = problems.start_block(p.n, block)
     s, _, _ = gpu_solver(p, max_iter=200)

@@ -35,23 +35,25 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 # The kernel behind the largest share of a 160^3 mixed iteration: the
-# LDS-staged Gram of the projected pencil, complex64 64 x 64 over 4096000 rows
+# Gram of the projected pencil, complex64 64 x 64 over 4096000 rows
 # on the FP64 MFMA, timed on its own at the solver's shape.
 DOMINANT_KERNEL_PROBE = "Gram c64 64x64"
 # HBM-side bytes per launch of that probe from rocprofv3 (FETCH_SIZE scaled
 # by 2.000 and WRITE_SIZE by 1.000, the factors being what the same counters
-# read for a 256 MiB device copy), valid only for the kernels.hip whose
-# SHA-256 prefix is recorded with it; any later change to that file makes the
+# read for a 256 MiB device copy), valid only for the kernel sources whose
+# SHA-256 prefix is recorded with it; any later change to them makes the
 # reported traffic null until the counters are taken again.
-DOMINANT_KERNEL_TRAFFIC = 4261221332          # bytes per launch
-DOMINANT_KERNEL_TRAFFIC_SRC = "32cf1a236323714d"   # sha256 prefix of kernels.hip
+DOMINANT_KERNEL_TRAFFIC = 4262329088          # bytes per launch
+DOMINANT_KERNEL_TRAFFIC_SRC = "bcbfc85d30952bc0"   # sha256 prefix of the Gram's sources
 
 
 def kernels_source_sha():
     import hashlib
-    path = os.path.join(ROOT, "paper_1506_06829_amd", "csrc", "kernels.hip")
-    with open(path, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in ("device_math.h", "gram.h", "gram.hip", "gram_c64.hip"):
+        with open(os.path.join(ROOT, "paper_1506_06829_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 METRIC = "time to k eigenpairs @1e-10 rel. residual, mixed vs FP64; SpMM HBM GB/s"

@@ -1,6 +1,7 @@
-// HIP kernels (gfx950) for the GPLHR block iteration: CSR sparse-times-block
-// products, row-local block updates, the Cholesky-QR factor, residual norms
-// and the one-time operator setup.  (Gram matrices: gram.h.)
+// HIP kernels (gfx950) for the GPLHR block iteration: the launch and the general
+// kernels of row-local block updates (the streaming one: update.h), the
+// Cholesky-QR factor, residual norms and the one-time operator setup.  (Sparse
+// products: spmm.h.  Gram matrices: gram.h.)
 //
 // Layout: every n-by-w block is row-major ("block-row interleaved"): row i of
 // a block is w contiguous complex values, so a sparse-row gather reads whole

@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
     const int e0 = __builtin_amdgcn_readfirstlane(a.rp[row0]);
     const int ne = __builtin_amdgcn_readfirstlane(a.rp[row0 + nr]) - e0;
     const bool staged = ne <= WS;
-    const uint32_t rowb = (uint32_t)a.ldx * (uint32_t)sizeof(T);
+    const std::conditional_t<S32, uint32_t, uint64_t> rowb = (uint64_t)a.ldx * sizeof(T);
     if (staged) {
         int32_t rp = 0, ci[WS / 64];
         typedef decltype(T::x) vec __attribute__((ext_vector_type(2)));
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
 #pragma unroll
         for (int q = 0; q < WS / 64; ++q)
             if (64 * q < ne) {
-                w_ci[64 * q + lane] = S32 ? (uint32_t)ci[q] * rowb : (uint32_t)ci[q];
+                w_ci[64 * q + lane] = S32 ? (uint32_t)(ci[q] * rowb) : (uint32_t)ci[q];
                 reinterpret_cast<vec *>(w_val)[64 * q + lane] = val[q];
             }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
         uint32_t j[BATCH];
         auto block_row = [&](int u) {
             if constexpr (S32) load_vec<T, CPL>(reinterpret_cast<const T *>(X + (j[u] + cb)), x[u]);
-            else load_vec<T, CPL>(reinterpret_cast<const T *>(X + (uint64_t)j[u] * rowb + cb), x[u]);
+            else load_vec<T, CPL>(reinterpret_cast<const T *>(X + j[u] * rowb + cb), x[u]);
         };
         // entries past the row's end (p1) repeat its last one; its block row is
         // loaded again where that is cheaper than masked loads (short rows: 160^3
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
              std::true_type{});
     else
         walk(a.rp[row], a.rp[row + 1],
-             [&](int e) { return S32 ? (uint32_t)a.ci[e] * rowb : (uint32_t)a.ci[e]; },
+             [&](int e) { return S32 ? (uint32_t)(a.ci[e] * rowb) : (uint32_t)a.ci[e]; },
              [&](int e) { return value_of(e, MODE == 3 ? a.ci[e] : 0); }, std::false_type{});
     T out[CPL];
     if constexpr (MODE == 0) {
@@ -336,25 +336,34 @@ static void spmm_launch(hipStream_t st, SpmmArgs<T> a, int mode, int plane, int6
     } else if (b > 64 || (row_len > 12 && (row_len <= 17 || b > 16) && n * b >= (1 << 20))) {
         cpl = b % 2 == 0 ? 2 : 1;
     }
-    a.lpr = (b + cpl - 1) / cpl;
-    if (a.lpr > 64) throw Error(-1, "spmm: block too wide");
-    a.inv = (65536 + a.lpr - 1) / a.lpr;
-    a.rpw = 64 / a.lpr;
-    // fewer rows per wavefront where that brings its entries (and a quarter more,
-    // as rows differ) into the stage and keeps half of the lanes
-    const int64_t fit = (int64_t)SPMM_STAGE<T> * 4 / (5 * std::max<int64_t>(row_len, 1));
-    if (a.rpw > fit && 2 * fit >= a.rpw) a.rpw = (int)fit;
-    a.rpb = 4 * a.rpw;
-    a.nbs = (int)((n + 8 * (int64_t)a.rpb - 1) / (8 * (int64_t)a.rpb));
-    int64_t grid = 8 * (int64_t)a.nbs;
-    if (plane > 0) {
-        // workgroups stay within a slab and share its rows evenly
-        a.sp = plane;
-        a.ss = plane / 8;
-        a.nbs = (a.ss + a.rpb - 1) / a.rpb;
-        a.rpb = (a.ss + a.nbs - 1) / a.nbs;
-        a.rpw = (a.rpb + 3) / 4;
-        grid = (int64_t)8 * a.nbs * (n / plane);
+    const auto shape = [&](int cols, int pl, bool fits) -> int64_t {
+        a.lpr = (b + cols - 1) / cols;
+        if (a.lpr > 64) throw Error(-1, "spmm: block too wide");
+        a.inv = (65536 + a.lpr - 1) / a.lpr;
+        a.rpw = 64 / a.lpr;
+        // fewer rows per wavefront where that brings its entries (and a quarter more,
+        // as rows differ) into the stage and keeps half of the lanes
+        const int64_t fit = (int64_t)SPMM_STAGE<T> * 4 / (5 * std::max<int64_t>(row_len, 1));
+        if (fits && a.rpw > fit && 2 * fit >= a.rpw) a.rpw = (int)fit;
+        a.rpb = 4 * a.rpw;
+        a.sp = pl;
+        if (pl > 0) {
+            // workgroups stay within a slab and share its rows evenly
+            a.ss = pl / 8;
+            a.nbs = (a.ss + a.rpb - 1) / a.rpb;
+            a.rpb = (a.ss + a.nbs - 1) / a.nbs;
+            a.rpw = (a.rpb + 3) / 4;
+            return (int64_t)8 * a.nbs * (n / pl);
+        }
+        a.nbs = (int)((n + 8 * (int64_t)a.rpb - 1) / (8 * (int64_t)a.rpb));
+        return 8 * (int64_t)a.nbs;
+    };
+    int64_t grid = shape(cpl, plane, true);
+    // a launch has less than 2^32 threads: beyond that (tiny planes, wide blocks of
+    // 10^8 rows), as few workgroups as the rows allow
+    if (grid >= (int64_t)1 << 24) {
+        if (sizeof(T) == 16 && b % 2 == 0) cpl = 2;
+        grid = shape(cpl, 0, false);
     }
     const int rl = (int)std::min<int64_t>(row_len, 1 << 20);
     if (mode == 0) spmm_batch<T, 0>(st, a, cpl, (int)grid, rl);

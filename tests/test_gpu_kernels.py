@@ -224,6 +224,23 @@ def test_spmm_row_lengths(device, b, dtype, lengths):
     assert np.all(np.abs(Y - ref) <= 4 * (max(lengths) + 2) * eps * scale)
 
 
+def test_spmm_of_many_tiny_planes(device):
+    # planes of 8 rows: more workgroups than a launch takes, so the rows run in
+    # natural order; the result is the same
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    n = 8 * ((1 << 21) + 5)
+    rp = torch.arange(n + 1, dtype=torch.int32, device=device)
+    g = torch.Generator(device=device).manual_seed(2)
+    v = torch.randn(n, dtype=torch.complex128, device=device, generator=g)
+    A = G.DeviceCsr(n, rp, rp[:n].flip(0).contiguous(), v)
+    X = torch.randn((n, 2), dtype=torch.complex128, device=device, generator=g)
+    Y = G.spmm(A, X, plane=8)
+    assert torch.equal(Y, G.spmm(A, X))
+    ref = v[:, None] * X.flip(0)
+    assert float((Y - ref).abs().max()) < 1e-14 * float(ref.abs().max())
+
+
 def test_spmm_of_rows_far_apart(device):
     # a block that spans more than 32-bit byte offsets
     import torch

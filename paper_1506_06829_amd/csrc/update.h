@@ -31,6 +31,7 @@
 // later group are other rows), so Out may alias any input.
 #pragma once
 #include "device_math.h"
+#include "update_cols.h"
 
 namespace gplhr {
 
@@ -137,7 +138,8 @@ void update_stream_kernel(UpdArgs<T> a, int nslab, int nts) {
     const uint32_t w0 = __builtin_amdgcn_readfirstlane(blockIdx.x * a.waves + wave);
     // per slab: the next group's first row (advanced by the scalar unit) and
     // the byte offsets of the lane's two entries in a group; entries past the
-    // term's width read its first one (pair) and enter as zeros
+    // term's width read its slab's first one (complex64 in pairs: first pair)
+    // and enter as zeros
     const char *next[SL];
     uint32_t off[SL][2];
 #pragma unroll
@@ -147,7 +149,7 @@ void update_stream_kernel(UpdArgs<T> a, int nslab, int nts) {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
             off[i][h] = (uint32_t)(li * sb.ldb) +
-                        (uint32_t)((!RAG || 2 * lk + h < sb.lim ? 2 * lk + h : VEC ? h : 0) * sizeof(T));
+                        (uint32_t)(upd_slab_column(RAG ? sb.lim : 8, lk, h, VEC && sizeof(T) == 8) * sizeof(T));
     }
     // Output pieces.  A lane's registers hold pieces of row li that are 64 bytes
     // of a tile apart (complex128: entries lk and 4 + lk) or in two neighbouring

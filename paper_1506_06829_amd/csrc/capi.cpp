@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "driver.h"
+#include "gram_split.h"
 
 struct gplhr_ctx {
     gplhr::Ctx c;
@@ -48,6 +49,7 @@ gplhr_status guard(gplhr_t h, F &&f) {
 namespace {
 std::mutex g_gram_mu;
 std::map<std::pair<int, hipStream_t>, std::pair<double2 *, size_t>> g_gram_part;
+constexpr size_t MAX_GRAM_PART = (size_t)4 << 20;   // entries: 64 MiB
 }  // namespace
 
 extern "C" {
@@ -383,7 +385,7 @@ gplhr_status gplhr_gram(int dtype, int64_t n, const void *X, int ldx, int bx, co
             (dtype != 0 && dtype != 1) || !X || !Y || !G)
             throw gplhr::Error(-1, "gplhr_gram: bad arguments");
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
-        const size_t cap = gplhr::gram_part_entries(bx, by);
+        const size_t cap = std::min(gplhr::gram_part_entries(INT64_MAX, bx, by), MAX_GRAM_PART);
         int dev = 0;
         GPLHR_HIP_CHECK(hipGetDevice(&dev));
         std::lock_guard<std::mutex> lock(g_gram_mu);
@@ -419,7 +421,9 @@ gplhr_status gplhr_proj_orth(int dtype, int64_t n, void *Z, int ld, int wy, int 
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
         const int wg = wy + w;
         // one allocation: Gram partials | G = [Y X]^H X | R^{-1} | C_Y | counter
-        const size_t cap = gplhr::gram_part_entries(wg, w);
+        // (what these rows' partials take: the runtime maps and unmaps it on every
+        // call, about 4 us a MiB)
+        const size_t cap = gplhr::gram_part_entries(n, wg, w);
         const size_t nG = (size_t)wg * w, nR = (size_t)w * w, nC = (size_t)std::max(wy, 1) * w;
         double2 *buf = nullptr;
         GPLHR_HIP_CHECK(hipMallocAsync((void **)&buf, sizeof(double2) * (cap + nG + nR + nC + 1), st));

@@ -1,5 +1,6 @@
 // Launch of the Gram kernels (gram.h): shape, row split and reduction.
 #include "gram.h"
+#include "gram_split.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -115,11 +116,6 @@ __global__ __launch_bounds__(1024) void gram_tile_kernel(GramArgs<T> a) {
     }
 }
 
-size_t gram_part_entries(int bx, int by) {
-    const size_t tiles = (size_t)((bx + 7) / 8 + 1) * ((by + 7) / 8);
-    return std::min<size_t>(1024 * tiles, 32768) * 128;
-}
-
 template <typename T>
 static void launch_gram_impl(hipStream_t st, int64_t n, const T *X, int ldx, int bx, const T *Y, int ldy, int by,
                              const T *yscale, double2 *part, size_t part_cap, double2 *out, int ldo,
@@ -134,7 +130,7 @@ static void launch_gram_impl(hipStream_t st, int64_t n, const T *X, int ldx, int
         GPLHR_HIP_CHECK(hipGetLastError());
         return;
     }
-    auto units = [](int w) { return (w + 7) / 8; };
+    const auto units = gram_units;
     GramFn<T> fn = nullptr;
     if (Y2) {
         a.ma = units(bx); a.mb1 = units(by1); a.mb = a.mb1 + units(by - by1);
@@ -165,23 +161,13 @@ static void launch_gram_impl(hipStream_t st, int64_t n, const T *X, int ldx, int
     // X^H X takes the path of X^H Y of its width, so that the same block passed as
     // a copy gives the same bits
     const int tiles = a.tri && a.ma1 == 0 ? a.ma * a.mb : a.ntile;
-    if (n <= 1024 || (n <= 2048 && tiles > 16)) {
+    if (gram_few_rows(n, tiles)) {
         hipLaunchKernelGGL(gram_tile_kernel<T>, dim3(a.ntile), dim3(1024), 0, st, a);
         GPLHR_HIP_CHECK(hipGetLastError());
         return;
     }
     const int ks = 4 / gram_groups(a.ma, a.mb, a.ma1, a.tri);
-    // Row blocks: one per 32 rows while that leaves CUs idle (a wave then has
-    // two K steps, both in flight at once; 1024 rows, complex128, 32 x 32: 8.7 us
-    // against 9.4 at 64 rows and 11.2 at 96), up to one per CU at 128 rows, then
-    // two per CU (more than 8 tiles: two waves per SIMD) or four.  The partials
-    // cost 2 KiB per tile and block, written and read: 262144 rows, complex128,
-    // 14 x 14 20.1 us with 1024 blocks and 15.1 with 256, 40 x 40 91 us with 256
-    // and 75 with 512; 4096000 rows, complex64, 16 x 16 118 us with 1024 blocks
-    // and 141 with 256; 20000 rows, 10 x 10 9.9 us with 256 blocks, 7.5 with 156.
-    const bool wide = tiles > 8;
-    int64_t nblk = std::max({std::min<int64_t>(128, n / 32), std::min<int64_t>(256, n / 128),
-                             std::min<int64_t>(wide ? 512 : 1024, n / (wide ? 512 : 1024)), (int64_t)1});
+    int64_t nblk = gram_row_blocks(n, tiles > 8);
     nblk = std::min<int64_t>(nblk, (int64_t)(part_cap / (128 * (size_t)a.ntile)));
     if (nblk < 1) throw Error(-1, "gram: partial buffer too small");
     a.rows_per_blk = ((n + nblk - 1) / nblk + 4 * ks - 1) / (4 * ks) * (4 * ks);

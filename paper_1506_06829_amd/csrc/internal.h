@@ -63,9 +63,9 @@ int spmm_plane(hipStream_t st, int64_t n, const int32_t *rp, const int32_t *ci);
 // G = X^H diag(yscale) Y (bx-by-by, FP64 accumulation, fixed reduction order)
 // written column-major with leading dimension ldo.  yscale (complex per row)
 // may be null (with a scale, X and Y need equally many units of 8 columns).
-// `part` is scratch of part_cap complex128 entries; gram_part_entries gives
-// the size at which no shape runs with fewer row blocks than it wants.
-size_t gram_part_entries(int bx, int by);
+// `part` is scratch of part_cap complex128 entries; gram_part_entries
+// (gram_split.h) gives the size at which no shape runs with fewer row blocks than
+// it wants.
 template <typename T>
 void launch_gram(hipStream_t st, int64_t n, const T *X, int ldx, int bx, const T *Y, int ldy,
                  int by, const T *yscale, double2 *part, size_t part_cap, double2 *out, int ldo);

@@ -1,0 +1,59 @@
+"""CPU test of a Gram's scratch (csrc/gram_split.h): it holds the partials of the
+row blocks the launch asks for, and a call that allocates it (gplhr_proj_orth,
+which pays for mapping it every time) takes no more than its rows need."""
+import subprocess
+from pathlib import Path
+
+import pytest
+
+ROOT = Path(__file__).resolve().parents[1]
+
+
+@pytest.fixture(scope="module")
+def split(tmp_path_factory):
+    exe = tmp_path_factory.mktemp("split") / "harness"
+    subprocess.run(["g++", "-O1", "-std=c++17", f"-I{ROOT / 'paper_1506_06829_amd' / 'csrc'}",
+                    str(ROOT / "tests" / "host_gram_split_harness.cpp"), "-o", str(exe)], check=True)
+    scratch, blocks = {}, {}
+    for l in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines():
+        k, *v = l.split()
+        v = list(map(int, v))
+        if k == "s":
+            scratch[v[0], v[1], v[2]] = v[3]
+        else:
+            blocks[v[0], v[1]] = (v[2], v[3])
+    return scratch, blocks
+
+
+def _tiles(bx, by):
+    """Tile counts a call of these widths can run with: X and Y apart (either as
+    the wider one), or Y the last by columns of X; with each, the count that
+    decides the row blocks."""
+    u = lambda w: (w + 7) // 8
+    yield u(bx) * u(by), u(bx) * u(by)
+    if bx >= by:
+        a, m = u(bx - by), u(by)
+        t = a * m + m * (m + 1) // 2
+        yield t, (t if a else m * m)
+
+
+def test_scratch_holds_the_wanted_row_blocks(split):
+    scratch, blocks = split
+    for (n, bx, by), have in scratch.items():
+        for tiles, rule in _tiles(bx, by):
+            few, want = blocks[n, rule]
+            assert few or have >= 128 * tiles * want, (n, bx, by, tiles)
+
+
+def test_scratch_of_a_projection_follows_its_rows(split):
+    # a tile's partial is 128 entries; one row block per 128 rows, but 128 of them
+    # from 4096 rows on and no more than 512 (8 tiles or fewer: 1024)
+    scratch, _ = split
+    for (n, wg, w), have in scratch.items():
+        if w > 48 or wg < w or wg - w > 48:
+            continue
+        tiles = ((wg + 7) // 8 + 1) * ((w + 7) // 8)
+        if n <= 1024:
+            assert have == 0
+        assert have <= 128 * tiles * max(128, n // 128), (n, wg, w)
+        assert have <= 128 * max(512 * tiles, 8 * 1024), (n, wg, w)

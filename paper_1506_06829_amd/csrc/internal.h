@@ -43,8 +43,8 @@ void pinned_free(void *p, size_t bytes);
 // in the plane-slab order (plane rows per plane; must divide n and be a
 // multiple of 8), 0 in natural order; the result is the same.  nnz (the
 // stored entries, rp[n]) sets how many entries of a row are gathered at once;
-// any value >= 0 gives the same result.  Y is left as it was where stop is not
-// null and holds a nonzero count.
+// any value >= 0 gives the same result.  Mode 1: Y is left as it was where stop is
+// not null and holds a nonzero count.
 template <typename T>
 void launch_spmm(hipStream_t st, int64_t n, const int32_t *rp, const int32_t *ci, const T *val,
                  const T *X, int ldx, T *Y, int ldy, int b, int mode, const T *Rhs, int ldr,

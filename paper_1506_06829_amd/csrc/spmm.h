@@ -11,6 +11,7 @@
 #include <type_traits>
 
 #include "device_math.h"
+#include "spmm_shape.h"
 
 namespace gplhr {
 
@@ -77,13 +78,7 @@ struct SpmmArgs {
     const T *dw;
     const double2 *dval, *dcs;        // MODE 3: C's values and dw
     const unsigned long long *stop;   // not null and not zero: leave Y alone
-    int lpr;        // lanes per row
-    int inv;        // ceil(65536 / lpr): lane / lpr as a multiplication
-    int rpw;        // rows per wavefront
-    int rpb;        // rows per workgroup
-    int sp;         // >0: plane-slab row schedule with planes of sp rows
-    int ss;         // slab: sp / 8 rows of each plane
-    int nbs;        // workgroups per slab of a plane
+    SpmmShape s;
     int nt;         // 1: non-temporal stores of Y
 };
 
@@ -127,35 +122,43 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
     __shared__ T s_val[4 * WS];
     __shared__ int32_t s_rp[260];
     const int tid = threadIdx.x, lane = tid & 63;
-    if (a.stop && *a.stop) return;
+    if constexpr (MODE == 1 || MODE == 3)   // (the modes that are launched with one)
+        if (a.stop && *a.stop) return;
     auto value_of = [&](int e, int32_t j) {
         if constexpr (MODE == 3) return from_d<T>(cmul(a.dval[e], a.dcs[j]));
         else return a.val[e];
     };
-    // the workgroup's rows: row0 .. row0 + nr - 1
-    int64_t row0;
-    int nr;
-    if (a.sp > 0) {
-        // XCD x takes slab x of every plane, planes in order
-        const uint32_t x = blockIdx.x & 7, k = blockIdx.x >> 3, z = k / (uint32_t)a.nbs;
-        const int i = (int)(k - z * a.nbs) * a.rpb;
-        row0 = (int64_t)z * a.sp + (int64_t)x * a.ss + i;
-        nr = min(a.rpb, a.ss - i);
-    } else {
-        // XCD x takes the x-th eighth of the blocks
-        const int64_t k = (int64_t)(blockIdx.x & 7) * a.nbs + (blockIdx.x >> 3);
-        row0 = k * a.rpb;
-        nr = (int)min((int64_t)a.rpb, a.n - row0);
-    }
+    // this wavefront's rows, row0 .. row0 + nr - 1, and entries, ne from e0 on
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    row0 += wv * a.rpw;
-    nr = min(a.rpw, nr - wv * a.rpw);
-    if (nr <= 0) return;
+    const auto mine = [&](SpmmRows r) {
+        return SpmmRows{r.row0 + wv * a.s.rpw, min(a.s.rpw, r.nr - wv * a.s.rpw)};
+    };
+    const bool check = a.s.order == SPMM_CHECK;
+    int ends = 0;   // lanes 0 .. 8: the row pointers at the eighths' ends
+    if (check) ends = a.rp[min(min(lane, 8) * ((uint32_t)a.s.nbs * (uint32_t)a.s.rpb), (uint32_t)a.n)];
+    SpmmRows rows = mine(a.s.sp > 0 ? spmm_plane_rows(a.s, blockIdx.x)
+                                    : spmm_natural_rows(a.s, a.n, blockIdx.x, a.s.order != SPMM_TURN));
+    const auto entries = [&](const SpmmRows &r, int &first, int &count) {
+        const int64_t r0 = min(r.row0, a.n);
+        first = __builtin_amdgcn_readfirstlane(a.rp[r0]);
+        count = __builtin_amdgcn_readfirstlane(a.rp[r0 + max(r.nr, 0)]) - first;
+    };
+    int e0, ne;
+    entries(rows, e0, ne);
+    if (check) {
+        const int more = __builtin_amdgcn_update_dpp(0, ends, 0x101, 0xf, 0xf, false) - ends;   // entries of eighth `lane`
+        const int total = __builtin_amdgcn_readlane(ends, 8) - __builtin_amdgcn_readfirstlane(ends);
+        if (__ballot(lane < 8 && !spmm_even(more, total))) {
+            rows = mine(spmm_natural_rows(a.s, a.n, blockIdx.x, false));
+            entries(rows, e0, ne);
+        }
+    }
+    if (rows.nr <= 0) return;
+    const int64_t row0 = rows.row0;
+    const int nr = rows.nr;
     uint32_t *w_ci = s_ci + wv * WS;
     T *w_val = s_val + wv * WS;
     int32_t *w_rp = s_rp + wv * 65;
-    const int e0 = __builtin_amdgcn_readfirstlane(a.rp[row0]);
-    const int ne = __builtin_amdgcn_readfirstlane(a.rp[row0 + nr]) - e0;
     const bool staged = ne <= WS;
     const std::conditional_t<S32, uint32_t, uint64_t> rowb = (uint64_t)a.ldx * sizeof(T);
     if (staged) {
@@ -189,7 +192,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    const int r = (lane * a.inv) >> 16, c0 = (lane - r * a.lpr) * CPL;
+    const int r = (lane * a.s.inv) >> 16, c0 = (lane - r * a.s.lpr) * CPL;
     if (r >= nr || c0 >= a.b) return;
     const int64_t row = row0 + r;
 
@@ -210,12 +213,13 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
     for (int u = 0; u < CPL; ++u) acc[u] = czero<T>();
     const char *__restrict__ X = reinterpret_cast<const char *>(a.X);
     const uint32_t cb = (uint32_t)c0 * (uint32_t)sizeof(T);
-    // entries p .. p + BATCH - 1 of the row; those past its end leave the sums
+    // entries p .. p + NB - 1 of the row; those past its end leave the sums
     // alone, wherever their loads point (NaN there must not reach them)
     auto batch = [&](int p, int p1, auto index, auto value, auto full, auto lds) {
         constexpr bool FULL = decltype(full)::value, LDS = decltype(lds)::value;
-        T x[BATCH][CPL], v[BATCH];
-        uint32_t j[BATCH];
+        constexpr int NB = BATCH;
+        T x[NB][CPL], v[NB];
+        uint32_t j[NB];
         auto block_row = [&](int u) {
             if constexpr (S32) load_vec<T, CPL>(reinterpret_cast<const T *>(X + (j[u] + cb)), x[u]);
             else load_vec<T, CPL>(reinterpret_cast<const T *>(X + j[u] * rowb + cb), x[u]);
@@ -226,18 +230,18 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
         // entries, 10 columns: 76 against 73.5)
         auto at = [&](int u) { return FULL ? p + u : min(p + u, p1 - 1); };
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u) j[u] = index(at(u));
+        for (int u = 0; u < NB; ++u) j[u] = index(at(u));
         if constexpr (!LDS)
 #pragma unroll
-            for (int u = 0; u < BATCH; ++u) v[u] = value(at(u));
+            for (int u = 0; u < NB; ++u) v[u] = value(at(u));
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u)
-            if (FULL || BATCH <= 7 || p + u < p1) block_row(u);
+        for (int u = 0; u < NB; ++u)
+            if (FULL || NB <= 7 || p + u < p1) block_row(u);
         if constexpr (LDS)
 #pragma unroll
-            for (int u = 0; u < BATCH; ++u) v[u] = value(at(u));
+            for (int u = 0; u < NB; ++u) v[u] = value(at(u));
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u)
+        for (int u = 0; u < NB; ++u)
 #pragma unroll
             for (int c = 0; c < CPL; ++c) {
                 T s = acc[c];
@@ -246,8 +250,9 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
             }
     };
     auto walk = [&](int p, int p1, auto index, auto value, auto lds) {
-        for (; p < p1; p += BATCH) {
-            if (__all(p + BATCH <= p1)) batch(p, p1, index, value, std::true_type{}, lds);
+        constexpr int NB = BATCH;
+        for (; p < p1; p += NB) {
+            if (__all(p + NB <= p1)) batch(p, p1, index, value, std::true_type{}, lds);
             else batch(p, p1, index, value, std::false_type{}, lds);
         }
     };
@@ -273,10 +278,12 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
     else store_vec<T, CPL>(a.Y + row * a.ldy + c0, out);
 }
 
-// Row schedule.  Without a plane, XCD x runs the x-th eighth of the rows, so that
-// rows gathered by neighbouring blocks are fetched into one L2 (dealt round robin,
-// each XCD fetched nearly every block row: 45^3 operator, 16 complex64 columns
-// 11.4 us, now 7.3; 10 complex128 16.4 and 9.4; random patterns the same).  With a
+// Row schedule.  Without a plane, XCD x runs the x-th eighth of the rows where the
+// eighths have about the same number of entries, so that rows gathered by
+// neighbouring blocks are fetched into one L2 (in turn, each XCD fetches nearly
+// every block row: 45^3 operator, 16 complex64 columns 11.4 us, by eighths 7.3 to
+// 8.1; 10 complex128 16.4 and 9.6; random patterns the same), else they run in turn
+// (spmm_even).  With a
 // plane of P rows (all couplings within +-P rows, n a multiple of P, P a multiple
 // of 8), XCD x runs slab x (rows x P/8 ... (x+1) P/8 - 1) of every plane, plane
 // after plane: the three planes of one slab that a block touches fit in that XCD's
@@ -336,35 +343,10 @@ static void spmm_launch(hipStream_t st, SpmmArgs<T> a, int mode, int plane, int6
     } else if (b > 64 || (row_len > 12 && (row_len <= 17 || b > 16) && n * b >= (1 << 20))) {
         cpl = b % 2 == 0 ? 2 : 1;
     }
-    const auto shape = [&](int cols, int pl, bool fits) -> int64_t {
-        a.lpr = (b + cols - 1) / cols;
-        if (a.lpr > 64) throw Error(-1, "spmm: block too wide");
-        a.inv = (65536 + a.lpr - 1) / a.lpr;
-        a.rpw = 64 / a.lpr;
-        // fewer rows per wavefront where that brings its entries (and a quarter more,
-        // as rows differ) into the stage and keeps half of the lanes
-        const int64_t fit = (int64_t)SPMM_STAGE<T> * 4 / (5 * std::max<int64_t>(row_len, 1));
-        if (fits && a.rpw > fit && 2 * fit >= a.rpw) a.rpw = (int)fit;
-        a.rpb = 4 * a.rpw;
-        a.sp = pl;
-        if (pl > 0) {
-            // workgroups stay within a slab and share its rows evenly
-            a.ss = pl / 8;
-            a.nbs = (a.ss + a.rpb - 1) / a.rpb;
-            a.rpb = (a.ss + a.nbs - 1) / a.nbs;
-            a.rpw = (a.rpb + 3) / 4;
-            return (int64_t)8 * a.nbs * (n / pl);
-        }
-        a.nbs = (int)((n + 8 * (int64_t)a.rpb - 1) / (8 * (int64_t)a.rpb));
-        return 8 * (int64_t)a.nbs;
-    };
-    int64_t grid = shape(cpl, plane, true);
-    // a launch has less than 2^32 threads: beyond that (tiny planes, wide blocks of
-    // 10^8 rows), as few workgroups as the rows allow
-    if (grid >= (int64_t)1 << 24) {
-        if (sizeof(T) == 16 && b % 2 == 0) cpl = 2;
-        grid = shape(cpl, 0, false);
-    }
+    if ((b + cpl - 1) / cpl > 64) throw Error(-1, "spmm: block too wide");
+    int64_t grid = 0;
+    a.s = spmm_launch_shape(n, b, cpl, sizeof(T) == 16 && b % 2 == 0 ? 2 : cpl, plane, row_len, SPMM_STAGE<T>,
+                            true, grid);
     const int rl = (int)std::min<int64_t>(row_len, 1 << 20);
     if (mode == 0) spmm_batch<T, 0>(st, a, cpl, (int)grid, rl);
     else if (mode == 1) spmm_batch<T, 1>(st, a, cpl, (int)grid, rl);

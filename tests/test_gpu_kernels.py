@@ -256,6 +256,42 @@ def test_spmm_of_rows_far_apart(device):
     assert np.all(np.abs(Y - A @ x) <= 4 * (n + 2) * 2.3e-16 * (abs(A) @ np.abs(x)))
 
 
+@pytest.mark.parametrize("b", [2, 10, 16, 24, 40])
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("rows", ["first", "sorted", "even", "long"])
+def test_spmm_of_unevenly_spread_entries(device, b, dtype, rows):
+    # most entries in the first eighth of the rows, rising row lengths (both: rows in
+    # turn), even rows (by eighths), and a few rows that no stage holds among short
+    # ones.  A row of L entries sums L products: (L + 2) eps of the sum of moduli.
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    rng = np.random.default_rng(b)
+    n = 20011
+    cnt = np.full(n, 5)
+    if rows == "first":
+        cnt[:n // 8] = 60
+    elif rows == "sorted":
+        cnt = np.sort(rng.integers(0, 30, n))
+    elif rows == "long":
+        cnt[::40] = 300
+    ip = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int32)
+    r = np.repeat(np.arange(n), cnt)
+    ci = rng.integers(0, n, ip[-1])
+    ci = ci[np.lexsort((ci, r))].astype(np.int32)
+    val = rng.standard_normal(ip[-1]) + 1j * rng.standard_normal(ip[-1])
+    X = _block(rng, n, b)
+    if dtype == "c64":
+        val, X = (z.astype(np.complex64).astype(np.complex128) for z in (val, X))
+    A = sp.csr_matrix((val, ci, ip), shape=(n, n))
+    tdt = torch.complex128 if dtype == "c128" else torch.complex64
+    dA = G.DeviceCsr(n, torch.as_tensor(ip).to(device), torch.as_tensor(ci).to(device),
+                     torch.as_tensor(val).to(device))
+    Y = G.spmm(dA, torch.as_tensor(X).to(device, tdt), val=dA.val.to(tdt)).cpu().numpy().astype(np.complex128)
+    eps = 2.3e-16 if dtype == "c128" else 1.2e-7
+    scale = abs(A) @ np.abs(X)
+    assert np.all(np.abs(Y - A @ X) <= 4 * (cnt.max() + 2) * eps * scale)
+
+
 @pytest.mark.parametrize("bx,by", [(1, 1), (5, 10), (10, 10), (16, 16), (30, 48), (48, 48), (64, 64),
                                    (40, 40), (40, 30), (40, 24), (33, 37)])
 @pytest.mark.parametrize("dtype", ["c128", "c64"])

@@ -115,6 +115,18 @@ struct SpmmArgs {
 // entries per wavefront
 template <typename T> constexpr int SPMM_STAGE = sizeof(T) == 16 ? 256 : 320;
 
+// The batch of unstaged rows, whose values take registers before the block rows do:
+// shorter where the whole one costs a wave per SIMD (30000 rows of 30, 16 complex64
+// columns 14.7 us with 17 in 136 VGPRs, 12.4 with 15 in 120; 262144 rows of 10 to
+// 14 in a band, 64 complex128 columns 325 with 12 in 170, 297 with 10 in 164; mode 3
+// with 17 complex128 entries took 312 registers).
+template <typename T, int CPL, int MODE, int BATCH>
+constexpr int spmm_unstaged() {
+    if (CPL == 1) return BATCH;
+    if (sizeof(T) == 8) return BATCH == 17 ? 15 : BATCH;
+    return BATCH == 12 ? 10 : BATCH == 17 && MODE == 3 ? 12 : BATCH;
+}
+
 template <typename T, int CPL, int MODE, int BATCH, bool S32>
 __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
     constexpr int WS = SPMM_STAGE<T>;
@@ -213,11 +225,12 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
     for (int u = 0; u < CPL; ++u) acc[u] = czero<T>();
     const char *__restrict__ X = reinterpret_cast<const char *>(a.X);
     const uint32_t cb = (uint32_t)c0 * (uint32_t)sizeof(T);
+    constexpr int UNSTAGED = spmm_unstaged<T, CPL, MODE, BATCH>();
     // entries p .. p + NB - 1 of the row; those past its end leave the sums
     // alone, wherever their loads point (NaN there must not reach them)
     auto batch = [&](int p, int p1, auto index, auto value, auto full, auto lds) {
         constexpr bool FULL = decltype(full)::value, LDS = decltype(lds)::value;
-        constexpr int NB = BATCH;
+        constexpr int NB = LDS ? BATCH : UNSTAGED;
         T x[NB][CPL], v[NB];
         uint32_t j[NB];
         auto block_row = [&](int u) {
@@ -250,7 +263,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
             }
     };
     auto walk = [&](int p, int p1, auto index, auto value, auto lds) {
-        constexpr int NB = BATCH;
+        constexpr int NB = decltype(lds)::value ? BATCH : UNSTAGED;
         for (; p < p1; p += NB) {
             if (__all(p + NB <= p1)) batch(p, p1, index, value, std::true_type{}, lds);
             else batch(p, p1, index, value, std::false_type{}, lds);

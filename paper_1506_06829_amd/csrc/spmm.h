@@ -309,7 +309,15 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
 // 5 or 7 slots (stencils of 5 and 7 points, without idle slots), 12 or 17.  17 is the
 // most the complex128 kernel with two columns per lane keeps within 256 VGPRs.
 // Measured at n = 262144, 17 random entries per row, 10 complex128 columns: 176 us
-// with 8 slots, 166 us with 12, 153 us with 17.
+// with 8 slots, 166 us with 12, 153 us with 17.  Shorter than that
+// - for rows of 8, whose 12 slots idle (60000 rows, 16 complex128 columns: 20.3 us
+//   with 12, 19.1 with 7; with few columns, where the entries' latency counts, 12: 4
+//   columns 6.7 and 7.3);
+// - for longer rows of blocks that stay in the L2, where the last batch's idle slots
+//   cost more than latencies (30000 rows of 1 to 60, 8 complex128 columns 20.1 with 17,
+//   17.4 with 7; not with few columns: 300000 rows of 30, one column 115 and 162), and
+//   for wide complex64 blocks of long rows (20000 rows of 100, 64 columns 80 with 17,
+//   69 with 5; beyond about 16 MB 100000 rows of 300, 24 columns 612 and 765).
 template <typename T, int MODE, int BATCH>
 static void spmm_go(hipStream_t st, const SpmmArgs<T> &a, int cpl, int grid) {
     // block rows and columns within 32-bit byte offsets
@@ -321,8 +329,11 @@ static void spmm_go(hipStream_t st, const SpmmArgs<T> &a, int cpl, int grid) {
 
 template <typename T, int MODE>
 static void spmm_batch(hipStream_t st, const SpmmArgs<T> &a, int cpl, int grid, int row_len) {
+    const double x = (double)a.n * a.b * sizeof(T);   // bytes the gathers spread over
     if (row_len <= 5) spmm_go<T, MODE, 5>(st, a, cpl, grid);
-    else if (row_len <= 7) spmm_go<T, MODE, 7>(st, a, cpl, grid);
+    else if (row_len <= 7 || (row_len == 8 && sizeof(T) == 16 && a.b >= 8)) spmm_go<T, MODE, 7>(st, a, cpl, grid);
+    else if (row_len > 17 && row_len <= 40 && a.b >= 8 && x <= 8e6) spmm_go<T, MODE, 7>(st, a, cpl, grid);
+    else if (row_len > 40 && sizeof(T) == 8 && a.b >= 24 && x <= 16e6) spmm_go<T, MODE, 5>(st, a, cpl, grid);
     else if (row_len <= 12) spmm_go<T, MODE, 12>(st, a, cpl, grid);
     else spmm_go<T, MODE, 17>(st, a, cpl, grid);
 }
@@ -342,10 +353,15 @@ static void spmm_launch(hipStream_t st, SpmmArgs<T> a, int mode, int plane, int6
     // Columns per lane: 16 bytes, two complex64 or one complex128 (the 160^3
     // operator, 16 complex64 columns: two beat one and four; 10 complex128 columns:
     // 425 us with one, 464 with two, as registers halve).  Two complex128 columns
-    // where a row is one batch of 13 to 17 entries and the blocks fill the chip
-    // (262144 rows of 17 random entries, 10 columns: 151 us against 154; longer rows
-    // want the wavefronts in flight, 60000 rows of 40: 59 against 56.5, up to wide
-    // blocks: with 32 columns 150 against 155).
+    // - where a row would leave lanes of its wavefront idle (22 to 24 columns, over 32:
+    //   us with one / two columns, 64^3 operator, 24 columns 53.9 / 47.4, 40 154 / 121);
+    // - with wide blocks of rows of more than 7 entries (24 columns, 262144 rows of 12 in
+    //   a band 99 / 76; 32 columns, 60000 rows of 40 156 / 150; 20000 rows of 25, 20
+    //   columns 16.7 / 19.0, 24 19.6 / 19.2), and from 16 columns on with rows that no
+    //   stage holds (16 columns, 30000 rows of 130 78.6 / 67.6; 50000 of 50 69.4 / 75.3);
+    // - where a row is one batch of 13 to 17 entries and the blocks fill the chip
+    //   (262144 rows of 17 random entries, 10 columns 154 / 151; longer rows want the
+    //   wavefronts in flight, 60000 rows of 40, 16 columns 71.7 / 73.8).
     const uintptr_t align = reinterpret_cast<uintptr_t>(a.X) | reinterpret_cast<uintptr_t>(a.Y) |
                             (mode != 0 ? reinterpret_cast<uintptr_t>(a.Rhs) : 0);
     int cpl = 1;
@@ -353,13 +369,14 @@ static void spmm_launch(hipStream_t st, SpmmArgs<T> a, int mode, int plane, int6
         const bool ok2 = (b % 2 == 0) && (a.ldx % 2 == 0) && (a.ldy % 2 == 0) &&
                          (mode == 0 || a.ldr % 2 == 0) && align % 16 == 0;
         cpl = ok2 ? 2 : 1;
-    } else if (b > 64 || (row_len > 12 && (row_len <= 17 || b > 16) && n * b >= (1 << 20))) {
+    } else if (b > 32 || (64 / b) * b < 50 || (row_len > 7 && b > 20) || (row_len > 50 && b >= 16) ||
+               (row_len > 12 && (row_len <= 17 || b > 16) && n * b >= (1 << 20))) {
         cpl = b % 2 == 0 ? 2 : 1;
     }
     if ((b + cpl - 1) / cpl > 64) throw Error(-1, "spmm: block too wide");
     int64_t grid = 0;
     a.s = spmm_launch_shape(n, b, cpl, sizeof(T) == 16 && b % 2 == 0 ? 2 : cpl, plane, row_len, SPMM_STAGE<T>,
-                            true, grid);
+                            sizeof(T) == 8 || cpl == 1 || row_len <= 17, grid);
     const int rl = (int)std::min<int64_t>(row_len, 1 << 20);
     if (mode == 0) spmm_batch<T, 0>(st, a, cpl, (int)grid, rl);
     else if (mode == 1) spmm_batch<T, 1>(st, a, cpl, (int)grid, rl);

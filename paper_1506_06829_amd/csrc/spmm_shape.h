@@ -61,9 +61,9 @@ inline SpmmShape spmm_shape(int64_t n, int b, int cols, int plane, int64_t row_l
     s.inv = (65536 + s.lpr - 1) / s.lpr;
     s.rpw = 64 / s.lpr;
     // fewer rows per wavefront where that brings its entries (and a quarter more, as
-    // rows differ) into the stage and keeps half of the lanes
+    // rows differ) into the stage and keeps half of the lanes; not with few, wide rows
     const int64_t fit = (int64_t)stage * 4 / (5 * std::max<int64_t>(row_len, 1));
-    if (cut && s.rpw > fit && 2 * fit >= s.rpw) s.rpw = (int)fit;
+    if (cut && s.rpw > 4 && s.rpw > fit && 2 * fit >= s.rpw) s.rpw = (int)fit;
     s.rpb = 4 * s.rpw;
     s.sp = plane;
     if (s.sp > 0) {

@@ -65,7 +65,12 @@ inline SpmmShape spmm_shape(int64_t n, int b, int cols, int plane, int64_t row_l
     const int64_t fit = (int64_t)stage * 4 / (5 * std::max<int64_t>(row_len, 1));
     if (cut && s.rpw > 4 && s.rpw > fit && 2 * fit >= s.rpw) s.rpw = (int)fit;
     s.rpb = 4 * s.rpw;
-    s.sp = plane;
+    // a plane whose slabs are less than four workgroups' rows would leave lanes idle at
+    // their ends; three of it fit an L2 whole, so that the natural order serves it as
+    // well (us, slabs / natural order: planes of 512 rows of 5 entries, complex64, 1
+    // column 12.6 / 8.7, 5 columns 21.3 / 16.3; of 4096 rows of 7 entries, 2 columns
+    // 8.1 / 7.2; at four workgroups' rows, planes of 512, 16 complex128 78.5 / 86.3)
+    s.sp = plane / 8 < 4 * s.rpb ? 0 : plane;
     if (s.sp > 0) {
         // workgroups stay within a slab and share its rows evenly
         s.ss = plane / 8;

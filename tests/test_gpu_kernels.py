@@ -292,6 +292,23 @@ def test_spmm_of_unevenly_spread_entries(device, b, dtype, rows):
     assert np.all(np.abs(Y - A @ X) <= 4 * (cnt.max() + 2) * eps * scale)
 
 
+@pytest.mark.parametrize("plane", [64, 512, 2048])
+@pytest.mark.parametrize("b", [1, 2, 5, 16])
+def test_spmm_of_thin_slabs(device, plane, b):
+    # planes whose slabs hold fewer rows than some workgroups take: in natural order,
+    # the same bits
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    n = 2048 * 21
+    A = sp.diags([1.0, -2.0, 4.0, 0.5, 3.0], [-plane, -1, 0, 1, plane], shape=(n, n), format="csr")
+    dA = G.DeviceCsr.from_host(problems.csr_from_scipy(A.astype(complex)))
+    x = _block(np.random.default_rng(b), n, b)
+    X = torch.as_tensor(x).to(device)
+    Y = G.spmm(dA, X, plane=plane)
+    assert torch.equal(Y, G.spmm(dA, X))
+    assert np.max(np.abs(Y.cpu().numpy() - A @ x)) < 7 * 2.3e-16 * 11 * np.abs(x).max()
+
+
 @pytest.mark.parametrize("bx,by", [(1, 1), (5, 10), (10, 10), (16, 16), (30, 48), (48, 48), (64, 64),
                                    (40, 40), (40, 30), (40, 24), (33, 37)])
 @pytest.mark.parametrize("dtype", ["c128", "c64"])

@@ -79,3 +79,16 @@ def test_no_check_where_it_cannot_pay(shapes):
     # few workgroups; one row to a wavefront; rows beyond 32 bits
     for n, b, want in ((12 ** 3, 16, "0"), (262144, 33, "1"), (1 << 31, 4, "1"), (262144, 32, "2")):
         assert shapes([f"x {n} {b} 1 1 0 7 320 1 0"])[0].split()[-1] == want
+
+
+def test_slabs_keep_their_lanes_busy(shapes):
+    # a plane whose slabs hold fewer than four workgroups' rows runs in natural order;
+    # where slabs are kept, no more than a quarter of the lanes wait at their ends
+    for plane in (512, 520, 1024, 2048, 4096, 25600):
+        n = plane * 64
+        for b in (1, 2, 4, 5, 10, 16, 33, 64):
+            grid, _, _, _, sp, _ = map(int, shapes([f"x {n} {b} 1 1 {plane} 7 256 1 0"])[0].split()[1:])
+            full = int(shapes([f"x {n} {b} 1 1 0 7 256 1 0"])[0].split()[4])
+            assert (sp == plane) == (plane // 8 >= 4 * full), (plane, b)
+            if sp:
+                assert grid * full <= 1.25 * n

@@ -377,6 +377,7 @@ static void spmm_launch(hipStream_t st, SpmmArgs<T> a, int mode, int plane, int6
     int64_t grid = 0;
     a.s = spmm_launch_shape(n, b, cpl, sizeof(T) == 16 && b % 2 == 0 ? 2 : cpl, plane, row_len, SPMM_STAGE<T>,
                             sizeof(T) == 8 || cpl == 1 || row_len <= 17, grid);
+    if (grid == 0) throw Error(-3, "spmm: more rows of this width than one launch takes");
     const int rl = (int)std::min<int64_t>(row_len, 1 << 20);
     if (mode == 0) spmm_batch<T, 0>(st, a, cpl, (int)grid, rl);
     else if (mode == 1) spmm_batch<T, 1>(st, a, cpl, (int)grid, rl);

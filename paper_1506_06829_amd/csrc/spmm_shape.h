@@ -92,7 +92,8 @@ inline SpmmShape spmm_shape(int64_t n, int b, int cols, int plane, int64_t row_l
 
 // The shape of one launch, which has less than 2^32 threads: where planes and lanes
 // would ask for more workgroups (tiny planes, wide blocks of 10^8 rows), as few as the
-// rows allow, `most` columns to a lane (cols is what it then runs with).
+// rows allow, `most` columns to a lane (cols is what it then runs with) and, for the
+// last few, not by eighths.  grid = 0: more rows than one launch takes.
 inline SpmmShape spmm_launch_shape(int64_t n, int b, int &cols, int most, int plane, int64_t row_len, int stage,
                                    bool cut, int64_t &grid) {
     constexpr int64_t limit = (int64_t)1 << 24;
@@ -100,6 +101,10 @@ inline SpmmShape spmm_launch_shape(int64_t n, int b, int &cols, int most, int pl
     if (grid < limit) return s;
     cols = most;
     s = spmm_shape(n, b, cols, 0, row_len, stage, false, grid);
+    if (grid < limit) return s;
+    s.order = SPMM_TURN;
+    grid = (n + s.rpb - 1) / s.rpb;
+    if (grid >= limit) grid = 0;
     return s;
 }
 

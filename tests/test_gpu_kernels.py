@@ -309,6 +309,28 @@ def test_spmm_of_thin_slabs(device, plane, b):
     assert np.max(np.abs(Y.cpu().numpy() - A @ x)) < 7 * 2.3e-16 * 11 * np.abs(x).max()
 
 
+def test_spmm_of_the_last_rows_one_launch_takes(device):
+    # one row to a wavefront: 2^24 - 1 workgroups, which the eighths would round up to
+    # 2^24 and beyond a launch; four rows more are refused
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    n, b = 4 * ((1 << 24) - 1), 33
+    rp = torch.arange(n + 5, dtype=torch.int32, device=device)
+    ci = rp[:n].flip(0).contiguous()
+    v = torch.full((n + 4,), 2.0, dtype=torch.complex64, device=device)
+    X = torch.empty((n, b), dtype=torch.complex64, device=device)
+    X[:] = rp[:n, None].remainder(8191)
+    A = G.DeviceCsr(n, rp[:n + 1], ci, v[:n])
+    Y = G.spmm(A, X, val=v[:n])
+    for i in (0, 1, 3, n // 2, n - 4, n - 1):
+        assert bool((Y[i] == 2.0 * ((n - 1 - i) % 8191)).all()), i
+    assert bool((Y[:, b - 1] == 2.0 * ci.remainder(8191)).all())
+    del X, Y
+    with pytest.raises(G.GplhrError):
+        G.spmm(G.DeviceCsr(n + 4, rp, torch.zeros(n + 4, dtype=torch.int32, device=device), v),
+               torch.empty((n + 4, b), dtype=torch.complex64, device=device), val=v)
+
+
 @pytest.mark.parametrize("bx,by", [(1, 1), (5, 10), (10, 10), (16, 16), (30, 48), (48, 48), (64, 64),
                                    (40, 40), (40, 30), (40, 24), (33, 37)])
 @pytest.mark.parametrize("dtype", ["c128", "c64"])

@@ -92,3 +92,17 @@ def test_slabs_keep_their_lanes_busy(shapes):
             assert (sp == plane) == (plane // 8 >= 4 * full), (plane, b)
             if sp:
                 assert grid * full <= 1.25 * n
+
+
+def test_launches_below_2_to_the_32_threads(shapes):
+    def run(n, b, cols, most, plane):
+        grid, lpr, rpw, rpb, sp, order = map(int, shapes([f"x {n} {b} {cols} {most} {plane} 7 256 1 0"])[0].split()[1:])
+        assert grid < 1 << 24
+        return grid, rpb, order
+    rows = (1 << 24) - 1
+    # rows in turn take the last few, whose eighths would round up to 2^24 workgroups
+    assert run(4 * rows, 33, 1, 1, 0) == (rows, 4, 1)
+    assert run(4 * (rows - 8), 33, 1, 1, 0)[0] == rows - 7
+    assert run(4 * rows + 1, 33, 1, 1, 0)[0] == 0           # refused
+    assert run(4 * rows + 1, 64, 1, 2, 0)[1:] == (8, 2)     # two columns to a lane
+    assert run(8 * ((1 << 21) + 5), 2, 1, 2, 8)[2] == 2     # tiny planes: natural order

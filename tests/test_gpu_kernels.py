@@ -331,6 +331,22 @@ def test_spmm_of_the_last_rows_one_launch_takes(device):
                torch.empty((n + 4, b), dtype=torch.complex64, device=device), val=v)
 
 
+@pytest.mark.parametrize("ld", [1 << 28, (1 << 28) + 1, 1 << 30])
+def test_spmm_of_rows_further_apart_than_32_bits(device, ld):
+    # a row stride of 2^32 bytes and more (17 GB in all)
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    n, b = (2, 3) if ld == 1 << 30 else (5, 3)
+    rng = np.random.default_rng(6)
+    A = sp.csr_matrix(rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n)))
+    dA = G.DeviceCsr.from_host(problems.csr_from_scipy(A))
+    x = _block(rng, n, b)
+    X = torch.empty((n - 1) * ld + b, dtype=torch.complex128, device=device).as_strided((n, b), (ld, 1))
+    X.copy_(torch.as_tensor(x))
+    Y = G.spmm(dA, X).cpu().numpy()
+    assert np.all(np.abs(Y - A @ x) <= 4 * (n + 2) * 2.3e-16 * (abs(A) @ np.abs(x)))
+
+
 @pytest.mark.parametrize("bx,by", [(1, 1), (5, 10), (10, 10), (16, 16), (30, 48), (48, 48), (64, 64),
                                    (40, 40), (40, 30), (40, 24), (33, 37)])
 @pytest.mark.parametrize("dtype", ["c128", "c64"])

@@ -433,24 +433,47 @@ static bool update_stream(hipStream_t st, UpdArgs<T> a, int kpad) {
     k.scl = a.rs != nullptr;
     k.vec = sizeof(T) == 16 || pairs;
     k.tri = a.t[0].upper && pad8(a.t[0].w) == 8 * nt;
+    const size_t coef = (size_t)ns * 4 * nt * 64 * sizeof(typename UpdMma<T>::R);
+    const int rows = sizeof(T) == 8 && ns <= 2 ? 32 : 16;   // of a row group
+    const size_t lds = 160 * 1024, tile = (size_t)16 * rows * (nt * 8 * sizeof(T) / 16 + 1);
+    // Outputs larger than the last-level caches.  Stores of 128-byte pieces that are not
+    // whole cache lines leave half-written lines behind, and streamed past the caches
+    // they are worse (1400000 rows, 3 -> 47 complex128 343 and 604 us): there whole rows
+    // leave in runs, through a tile of LDS per wave, and are streamed (200).  That is for
+    // rows with gaps between them (57 -> 13 572 -> 443, 4096000 rows 10 -> 10 in rows of 40
+    // 581 -> 479), for outputs at least as wide as the inputs (without a gap narrower
+    // ones keep the pieces: 56 -> 28 421 in pieces, 432 in runs) and, on whole lines, for
+    // outputs twice as wide, whose writes are most of the traffic (6 -> 32 139 -> 110;
+    // 64 -> 32 473 and 494).  Beyond 40 tiles of coefficients the pieces are as fast.
+    const bool big = (double)a.n * a.wout * sizeof(T) > 256.0 * 1024 * 1024 && k.vec && !k.beta && !k.scl;
+    const auto on_line = [](uint64_t bytes) { return bytes % 128 == 0; };
+    const bool lines = on_line(reinterpret_cast<uintptr_t>(a.out + a.ocol)) && on_line(a.ldo * sizeof(T)) &&
+                       on_line(a.wout * sizeof(T)) &&
+                       (a.split >= a.wout || (on_line(a.split * sizeof(T)) &&
+                                              on_line(reinterpret_cast<uintptr_t>(a.out + a.ocol2))));
+    const bool gaps = a.ldo > a.wout;
+    // rows with gaps are written by one wave per SIMD, which keeps the open lines few
+    // (20 -> 15, 1800000 rows 222 us, with two 261; up to 2 slabs, and for 7 and 8 of
+    // complex64, the reads want the second: 56 -> 14 of 4096000 complex64 rows 755 and 691)
+    const bool one = gaps && ns >= 3 && (sizeof(T) == 16 || ns <= 6);
+    const int run_waves = one || coef + 4 * tile <= lds / 2 ? 4 : 8;
+    k.run = big && (lines ? nt >= 2 * ns : gaps || nt >= ns) && ns * nt <= 40 && coef + run_waves * tile <= lds &&
+            (int64_t)rows * a.ldo * (int64_t)sizeof(T) <= (int64_t)UINT32_MAX;
     const UpdFn<T> fn = update_pick<T>(nt, ns, k);
     if (!fn) return false;
-    const size_t shmem = (size_t)ns * 4 * nt * 64 * sizeof(typename UpdMma<T>::R);
     // Two waves per SIMD, persistent: more only spread the accesses (4096000
     // rows, 32 -> 16 complex64: 286 us against 300 at three and 303 at four).  As
     // one workgroup of eight waves per CU where the coefficients take more than
     // 40 KiB of LDS and there are rows to spare (they are formed once per
     // workgroup: 262144 rows, 56 -> 42 complex128 113 against 118 us), else as two
     // of four (1024 rows, 64 -> 32 complex128: 10.9 against 13.9 us).
-    a.waves = shmem > 40 * 1024 && a.n >= 65536 ? 8 : 4;
-    const int bpc = a.waves == 8 ? 1 : 2;
-    const int rows = sizeof(T) == 8 && ns <= 2 ? 32 : 16;   // of a row group
+    a.waves = k.run ? run_waves : coef > 40 * 1024 && a.n >= 65536 ? 8 : 4;
+    const size_t shmem = coef + (k.run ? a.waves * tile : 0);
+    const int bpc = a.waves == 8 || (k.run && one) ? 1 : 2;
     const int64_t groups = (a.n + rows - 1) / rows;
     const int grid = (int)std::min<int64_t>((groups + a.waves - 1) / a.waves, 256 * bpc);
     a.nw = grid * a.waves;
-    // outputs larger than the last-level caches stream past them
-    const int nts = (double)a.n * a.wout * sizeof(T) > 256.0 * 1024 * 1024;
-    launch_lds_kernel(fn, grid, a.waves * 64, shmem, st, a, ns, nts);
+    launch_lds_kernel(fn, grid, a.waves * 64, shmem, st, a, ns, (int)k.run);
     return true;
 }
 

@@ -94,13 +94,16 @@ __host__ __device__ __forceinline__ int pad8(int w) { return (w + 7) & ~7; }
 // offsets and leading dimensions).  A row group is 16 MT rows: MT = 2 for
 // complex64 of up to two slabs, whose 2 KiB per 16 rows leave too little in
 // flight (16 -> 16 columns, 4096000 rows: 232 us with one).
-template <typename T, int NT, int SL, bool BETA, bool TRI, bool RAG, bool SCL, bool VEC>
+// RUN: the outputs pass through a tile of LDS and leave row after row, past the caches if
+// nts (pieces never do: update_stream).
+template <typename T, int NT, int SL, bool BETA, bool TRI, bool RAG, bool SCL, bool VEC, bool RUN = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void update_stream_kernel(UpdArgs<T> a, int nslab, int nts) {
     using M = UpdMma<T>;
     using R = typename M::R;
     using V = typename M::V;
     constexpr int MT = sizeof(T) == 8 && SL == 2 ? 2 : 1, ROWS = 16 * MT;
+    static_assert(!RUN || (VEC && !BETA && !SCL), "runs of 16-byte pieces, overwriting");
     extern __shared__ double2 sh_upd_stream[];
     R *sM = reinterpret_cast<R *>(sh_upd_stream);   // [slab][step][tile][lane]
     {
@@ -157,7 +160,7 @@ void update_stream_kernel(UpdArgs<T> a, int nslab, int nts) {
     // that every store instruction writes 128 consecutive bytes of 8 rows: then
     // lane li holds piece li / 8 of rows li % 8 and 8 + li % 8.  (Complex64 entries
     // moved one by one, and a last odd tile, are stored from where they are.)
-    constexpr bool SWAP = VEC, PAIR = VEC && sizeof(T) == 8;
+    constexpr bool SWAP = VEC && !RUN, PAIR = SWAP && sizeof(T) == 8;
     constexpr int NP = PAIR ? NT / 2 : NT;   // exchanged pairs
     const int64_t ldob = (int64_t)a.ldo * sizeof(T);
     const int lp = li >> 3;
@@ -173,6 +176,23 @@ void update_stream_kernel(UpdArgs<T> a, int nslab, int nts) {
     for (int nt = SWAP ? (PAIR ? 2 * NP : NT) : 0; nt < NT; ++nt)
 #pragma unroll
         for (int h = 0; h < 2; ++h) oof[nt][h] = (uint32_t)(li * ldob) + col_off(nt * 8 + M::entry(h, lk));
+    // RUN: a wave's tile of ROWS rows of 16-byte pieces, and the places of the lane's
+    // piece of its it-th store in the tile and in Out
+    constexpr int PE = 16 / (int)sizeof(T), NIT = RUN ? ROWS * NT * 8 / PE / 64 : 1;
+    constexpr int LDT = NT * 8 / PE + 1;     // pieces of a tile row (odd: rows spread over the banks)
+    f4v *tile = nullptr;
+    uint32_t tof[NIT], gof[NIT], grow[NIT];
+    if constexpr (RUN) {
+        tile = reinterpret_cast<f4v *>(sM + nslab * 4 * NT * 64) + wave * (ROWS * LDT);
+        const int wp = a.wout / PE;
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const int e = it * 64 + lane, row = e / wp, c = e - row * wp;
+            tof[it] = row < ROWS ? row * LDT + c : 0;
+            grow[it] = row;
+            gof[it] = (uint32_t)(min(row, ROWS - 1) * ldob) + col_off(c * PE);
+        }
+    }
     const T beta = from_d<T>(a.beta);
     T x[SL][MT][2];
     auto load = [&](int i, int rows) {   // rows past the `rows` of the last, partial group repeat its last one
@@ -264,6 +284,44 @@ void update_stream_kernel(UpdArgs<T> a, int nslab, int nts) {
             o.x += beta.x * d.x - beta.y * d.y;
             o.y += beta.x * d.y + beta.y * d.x;
         };
+        if constexpr (RUN) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    const V d = acc[mt][nt];
+                    f4v *row = tile + (16 * mt + li) * LDT + nt * 8 / PE;
+                    if constexpr (sizeof(T) == 8) row[lk] = f4v{d[0], d[1], d[2], d[3]};
+                    else {
+                        row[lk] = __builtin_bit_cast(f4v, make_double2(d[0], d[1]));
+                        row[4 + lk] = __builtin_bit_cast(f4v, make_double2(d[2], d[3]));
+                    }
+                }
+            // LDS operations of a wave complete in order
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int it = 0; it < NIT; ++it)
+                if ((int)grow[it] < rows) {
+                    const f4v o = tile[tof[it]];
+                    f4v *dst = reinterpret_cast<f4v *>(po + gof[it]);
+                    // (empty asm: two plain branches would be merged into one store
+                    // without the hint)
+                    if (nts) {
+                        asm volatile("");
+                        __builtin_nontemporal_store(o, dst);
+                        asm volatile("");
+                    } else {
+                        *dst = o;
+                    }
+                }
+            // the next group's tile may not overtake these reads
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            return;
+        }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
@@ -303,10 +361,7 @@ void update_stream_kernel(UpdArgs<T> a, int nslab, int nts) {
                                 o = __builtin_bit_cast(f4v, e);
                             }
                         }
-                        if (mine(2 * mt + hf, q)) {
-                            if (nts) __builtin_nontemporal_store(o, at(2 * mt + hf, q));
-                            else *at(2 * mt + hf, q) = o;
-                        }
+                        if (mine(2 * mt + hf, q)) *at(2 * mt + hf, q) = o;
                     }
                 }
             }
@@ -320,10 +375,7 @@ void update_stream_kernel(UpdArgs<T> a, int nslab, int nts) {
                     if constexpr (BETA) add_beta(o, bd[mt][nt][h]);
                     if (mine1(mt, nt, h)) {
                         typedef R r2n __attribute__((ext_vector_type(2)));
-                        r2n *dst = reinterpret_cast<r2n *>(at1(mt, nt, h));
-                        const r2n v{o.x, o.y};
-                        if (nts) __builtin_nontemporal_store(v, dst);
-                        else *dst = v;
+                        *reinterpret_cast<r2n *>(at1(mt, nt, h)) = r2n{o.x, o.y};
                     }
                 }
         }
@@ -350,7 +402,7 @@ void update_stream_kernel(UpdArgs<T> a, int nslab, int nts) {
 
 template <typename T> using UpdFn = void (*)(UpdArgs<T>, int, int);
 struct UpdKind {
-    bool beta, tri, rag, scl, vec;
+    bool beta, tri, rag, scl, vec, run;
 };
 // The kernel for nt output tiles and sl slabs, or null.
 template <typename T> UpdFn<T> update_pick(int nt, int sl, UpdKind k);
@@ -367,6 +419,11 @@ UpdFn<T> update_pick_shape(UpdKind k) {
     }
     if (k.scl) return k.beta ? nullptr : update_stream_kernel<T, NT, SL, false, false, true, true, true>;
     if (k.beta) return update_stream_kernel<T, NT, SL, true, false, true, false, true>;
+    if (k.run) {
+        if constexpr (NT >= 2 && NT <= SL)
+            if (k.tri) return update_stream_kernel<T, NT, SL, false, true, true, false, true, true>;
+        return update_stream_kernel<T, NT, SL, false, false, true, false, true, true>;
+    }
     if constexpr (NT >= 2 && NT <= SL)
         if (k.tri)
             return k.rag ? update_stream_kernel<T, NT, SL, false, true, true, false, true>

@@ -586,6 +586,52 @@ def test_block_update_row_groups(device, wx, wy, off, dtype, beta):
         assert np.isnan(out[:, :off]).all() and np.isnan(out[:, off + wy:]).all()
 
 
+@pytest.mark.parametrize("wx,wy,pad", [(3, 47, 0), (7, 30, 6), (6, 32, 0), (20, 15, 1), (33, 31, 3), (57, 13, 6), (16, 30, 2),
+                                       (64, 33, 0), (40, 10, 30), (64, 32, 0)])
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_block_update_beyond_the_caches(device, wx, wy, pad, dtype):
+    # outputs over 256 MiB: rows that leave in runs or in pieces, with and without gaps,
+    # on and off cache lines; what lies between the rows stays.  wx products per entry:
+    # (wx + 4) eps of the sum of moduli, on the GPU's rows sampled from all parts.
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    tdt, eps, size = (torch.complex128, 2.3e-16, 16) if dtype == "c128" else (torch.complex64, 1.2e-7, 8)
+    g = torch.Generator(device=device).manual_seed(wx * 100 + wy)
+    n = (256 << 20) // (wy * size) + 1003
+    X = torch.randn(n, wx + pad, dtype=tdt, device=device, generator=g)
+    Y = torch.full((n, wy + pad), 7.0, dtype=tdt, device=device)
+    M = torch.randn(wx, wy, dtype=torch.complex128, device=device, generator=g)
+    out = Y[:, pad // 2:pad // 2 + wy]
+    G.block_update(X[:, :wx], M, out)
+    rows = torch.cat([torch.arange(0, 2000), torch.arange(n - 2000, n), torch.randint(0, n, (4000,))]).to(device)
+    x, o = X[rows, :wx].to(torch.complex128).cpu().numpy(), out[rows].to(torch.complex128).cpu().numpy()
+    m = M.cpu().numpy()
+    assert np.max(np.abs(o - x @ m) / (np.abs(x) @ np.abs(m))) < 2 * (wx + 4) * eps
+    assert bool((Y[:, :pad // 2] == 7.0).all()) and bool((Y[:, pad // 2 + wy:] == 7.0).all())
+    if pad == 0:    # the rows between the sampled ones: against the same rows as a small block
+        k = n // 3
+        part = torch.empty(20000, wy, dtype=tdt, device=device)
+        G.block_update(X[k:k + 20000].clone(), M, part)
+        assert bool(((part - out[k:k + 20000]).abs() <= 2 * (wx + 4) * eps * 64 * wx).all())
+
+
+@pytest.mark.parametrize("wy,w,dtype", [(15, 16, "c128"), (14, 18, "c64"), (9, 24, "c128")])
+def test_proj_orth_beyond_the_caches(device, wy, w, dtype):
+    # updates by a triangular factor whose outputs leave in runs, in place
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    tdt, eps, size = (torch.complex128, 2.3e-16, 16) if dtype == "c128" else (torch.complex64, 1.2e-7, 8)
+    g = torch.Generator(device=device).manual_seed(wy)
+    n = (256 << 20) // (w * size) + 777
+    Z = torch.randn(n, wy + w, dtype=tdt, device=device, generator=g)
+    G.proj_orth(Z[:, :wy], 0, wy)
+    Y = Z[:, :wy].clone()
+    G.proj_orth(Z, wy, w)
+    H = G.gram(Z, Z).cpu().numpy()
+    assert torch.equal(Z[:, :wy], Y)
+    assert np.max(np.abs(H - np.eye(wy + w))) < 100 * eps
+
+
 @pytest.mark.parametrize("w", [10, 16, 48])
 @pytest.mark.parametrize("dtype", ["c128", "c64"])
 def test_block_update_in_place(device, w, dtype):

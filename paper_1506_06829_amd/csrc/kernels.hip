@@ -433,6 +433,13 @@ static bool update_stream(hipStream_t st, UpdArgs<T> a, int kpad) {
     k.scl = a.rs != nullptr;
     k.vec = sizeof(T) == 16 || pairs;
     k.tri = a.t[0].upper && pad8(a.t[0].w) == 8 * nt;
+    // Complex64 entries moved one by one from few columns to many: update_mfma_kernel
+    // stores them as fast and has less to set up (us, it / this kernel: 7 -> 47, 200000
+    // rows 23 / 27; 1 -> 32 accumulated, 100000 rows 13.5 / 18.6; 15 -> 48, 948 rows 7.0 /
+    // 8.1), but not with odd rows in small blocks (5 -> 33, 3000 rows 5.5 / 4.9) and not
+    // with more to move (9 -> 47 accumulated, 1000000 rows 15 % slower).
+    const int64_t most = ns == 1 ? (k.beta ? 400000 : INT64_MAX) : k.beta || a.ldo % 2 == 0 ? 100000 : 0;
+    if (!k.vec && nt >= 4 && ns <= 2 && a.n < most && (a.n > 4096 || a.ldo % 2 == 0)) return false;
     const size_t coef = (size_t)ns * 4 * nt * 64 * sizeof(typename UpdMma<T>::R);
     const int rows = sizeof(T) == 8 && ns <= 2 ? 32 : 16;   // of a row group
     const size_t lds = 160 * 1024, tile = (size_t)16 * rows * (nt * 8 * sizeof(T) / 16 + 1);
@@ -452,11 +459,16 @@ static bool update_stream(hipStream_t st, UpdArgs<T> a, int kpad) {
                        (a.split >= a.wout || (on_line(a.split * sizeof(T)) &&
                                               on_line(reinterpret_cast<uintptr_t>(a.out + a.ocol2))));
     const bool gaps = a.ldo > a.wout;
-    // rows with gaps are written by one wave per SIMD, which keeps the open lines few
-    // (20 -> 15, 1800000 rows 222 us, with two 261; up to 2 slabs, and for 7 and 8 of
-    // complex64, the reads want the second: 56 -> 14 of 4096000 complex64 rows 755 and 691)
-    const bool one = gaps && ns >= 3 && (sizeof(T) == 16 || ns <= 6);
-    const int run_waves = one || coef + 4 * tile <= lds / 2 ? 4 : 8;
+    // Rows with gaps are written by one wave per SIMD, which keeps the open lines few (us,
+    // with two / one: 20 -> 15, 1800000 complex128 rows 261 / 222; 9 -> 25 214 / 177); two
+    // for up to 2 whole slabs and for 7 and 8 of complex64, whose reads want them (16 -> 29
+    // 257 / 277; 56 -> 14 of 4096000 complex64 rows 691 / 755); half a wave per SIMD where
+    // nearly all traffic is such rows (7 -> 30 in rows of 36 complex128 195 / 167; 6 -> 34 in
+    // rows of 40 complex64 137 / 101), but not if their ends fill 64-byte requests (6 ->
+    // 32 in rows of 36 complex128 119 / 159).
+    const bool one = gaps && (sizeof(T) == 16 ? ns >= 3 || (ns == 2 && k.rag) : ns >= 3 && ns <= 6);
+    const bool few = gaps && nt >= 2 * ns && (sizeof(T) == 8 ? ns <= 2 : ns == 1 && ((a.ldo | a.wout) & 3) != 0);
+    const int run_waves = few ? 2 : one || coef + 4 * tile <= lds / 2 ? 4 : 8;
     k.run = big && (lines ? nt >= 2 * ns : gaps || nt >= ns) && ns * nt <= 40 && coef + run_waves * tile <= lds &&
             (int64_t)rows * a.ldo * (int64_t)sizeof(T) <= (int64_t)UINT32_MAX;
     const UpdFn<T> fn = update_pick<T>(nt, ns, k);
@@ -469,7 +481,7 @@ static bool update_stream(hipStream_t st, UpdArgs<T> a, int kpad) {
     // of four (1024 rows, 64 -> 32 complex128: 10.9 against 13.9 us).
     a.waves = k.run ? run_waves : coef > 40 * 1024 && a.n >= 65536 ? 8 : 4;
     const size_t shmem = coef + (k.run ? a.waves * tile : 0);
-    const int bpc = a.waves == 8 || (k.run && one) ? 1 : 2;
+    const int bpc = a.waves == 8 || (k.run && (one || few)) ? 1 : 2;
     const int64_t groups = (a.n + rows - 1) / rows;
     const int grid = (int)std::min<int64_t>((groups + a.waves - 1) / a.waves, 256 * bpc);
     a.nw = grid * a.waves;

@@ -19,10 +19,15 @@
 // stored; rows past the end are a masked step of their own after the loop).
 //
 // The four waves of a workgroup form G tile groups times KS = 4 / G row
-// splits.  G = 1 up to 17 tiles, 2 up to 34, else 4 (at most 136 accumulator
+// splits.  G = 1 up to 21 tiles, 2 up to 34, else 4 (at most 168 accumulator
 // registers, two waves per SIMD); each group is a range of the tile list with
 // a body of its own, so that the groups differ by one tile at most.  The waves of one row
-// split read the same rows at about the same time, from L1.
+// split read the same rows at about the same time, from L1.  A range of a few whole
+// columns of the list reads all of A again, so one group is the better while its
+// accumulators fit (1200000 rows, us, two groups / one): complex128 47 x 21 326 / 229,
+// 40 x 32 308 / 247, 56 x 24 401 / 269, X's last 24 of 64 columns 371 / 229; complex64
+// 48 x 24 197 / 186, 40 x 32 210 / 200.  24 tiles in one group spill (complex64 48 x 32
+// 250 / 264).
 //
 // TRI: Y is X's last `w` columns (X^H X of a Cholesky-QR step, [Y X]^H X of a
 // projection): operands are loaded once, and of the Hermitian part only the
@@ -74,7 +79,9 @@ constexpr int gram_tiles(int ma, int mb, int a1, bool tri) {
             if (!tri || i - a1 <= j) ++t;
     return t;
 }
-constexpr int gram_groups(int tiles) { return tiles <= 17 ? 1 : tiles <= 34 ? 2 : 4; }
+// Most tiles of a wave (of a kernel with one tile group; two have 17, four 16).
+constexpr int GRAM_MAX_TILES = 21;
+constexpr int gram_groups(int tiles) { return tiles <= GRAM_MAX_TILES ? 1 : tiles <= 34 ? 2 : 4; }
 // Tile groups of a kernel.  X^H X of up to 5 units splits its rows as X^H Y of
 // those widths does, so that the same block passed as a copy gives the same bits.
 constexpr int gram_groups(int ma, int mb, int a1, bool tri) {
@@ -97,7 +104,7 @@ constexpr bool gram_quads(int ma, int mb, bool tri, bool scaled) {
 
 struct GramPlan {
     int n;             // tiles of the group
-    int ti[17], tj[17];
+    int ti[GRAM_MAX_TILES], tj[GRAM_MAX_TILES];
     bool ua[9], ub[9]; // units read
 };
 template <int MA, int MB, int A1, bool TRI>
@@ -227,7 +234,7 @@ __device__ __forceinline__ double other_part(double v) {
 // first part (MB: Y alone); SC0: the first B unit that takes the row scale (MB:
 // none); u0, v0: the first unit of A and of B (quadrants).
 template <typename T, int MA, int MB, int A1, bool TRI, int M1, int SC0, int GI, int KS>
-__device__ __forceinline__ void gram_rows(const GramArgs<T> &a, int kh, int u0, int v0, d4v (&acc)[17]) {
+__device__ __forceinline__ void gram_rows(const GramArgs<T> &a, int kh, int u0, int v0, d4v (&acc)[GRAM_MAX_TILES]) {
     using R = typename RealOf<T>::R;
     constexpr GramPlan P = gram_plan<MA, MB, A1, TRI>(GI);
     constexpr int PF = gram_pf<T, MA, MB, A1, TRI, SC0>();
@@ -348,7 +355,7 @@ void gram_kernel(GramArgs<T> a) {
     __shared__ double red[G == 4 ? 256 : G * 8 * 256];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int kh = wave / G, g = wave - kh * G;
-    d4v acc[17];
+    d4v acc[GRAM_MAX_TILES];
 #pragma unroll
     for (int t = 0; t < TMAX; ++t) acc[t] = d4v{0.0, 0.0, 0.0, 0.0};
     double *part = a.part + (int64_t)blockIdx.x * NT * 256;

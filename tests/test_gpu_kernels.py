@@ -452,6 +452,27 @@ def test_gram_of_odd_unit_counts(device, bx, by, dtype):
         assert np.max(np.abs(Gm - X.conj().T @ Y) / scale) < 4 * (n + 4) * 2.3e-16, n
 
 
+@pytest.mark.parametrize("bx,by,own", [(47, 21, False), (18, 41, False), (39, 29, False), (49, 24, False),
+                                       (57, 17, False), (45, 45, True), (43, 36, True), (46, 30, True), (62, 22, True)])
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_gram_of_18_to_24_tiles(device, bx, by, own, dtype):
+    # up to 21 tiles one wave holds all of them, from 22 on two share them: row
+    # counts around a K step, a wave's steps and a row block.  Bound as above:
+    # n products per entry.
+    import torch
+    from paper_1506_06829_amd import gplhr as G
+    tdt = torch.complex128 if dtype == "c128" else torch.complex64
+    g = torch.Generator(device="cpu").manual_seed(bx * 100 + by)
+    for n in (2049, 2051, 8195, 33001):
+        Xd = torch.randn(n, bx, dtype=tdt, generator=g).to(device)
+        Yd = Xd[:, bx - by:] if own else torch.randn(n, by, dtype=tdt, generator=g).to(device)
+        Gm = G.gram(Xd, Yd).cpu().numpy()
+        X, Y = Xd.cpu().numpy().astype(np.complex128), Yd.cpu().numpy().astype(np.complex128)
+        scale = np.abs(X).T @ np.abs(Y)
+        assert np.max(np.abs(Gm - X.conj().T @ Y) / scale) < 4 * (n + 4) * 2.3e-16, n
+        assert np.array_equal(Gm, G.gram(Xd, Yd).cpu().numpy()), n
+
+
 @pytest.mark.parametrize("bx,by,own", [(17, 9, False), (9, 17, False), (64, 64, False), (40, 16, True), (20, 20, True)])
 @pytest.mark.parametrize("dtype", ["c128", "c64"])
 def test_gram_of_few_rows(device, bx, by, own, dtype):

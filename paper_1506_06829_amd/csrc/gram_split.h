@@ -15,23 +15,32 @@ inline bool gram_few_rows(int64_t n, int tiles) { return n <= 1024 || (n <= 2048
 
 // Row blocks of the kernels with partials: one per 32 rows while that leaves CUs idle
 // (a wave then has two K steps, both in flight at once), up to one per CU at 128
-// rows, then two per CU (more than 8 tiles: two waves per SIMD) or four.  The
-// partials cost 2 KiB per tile and block, written and read: 262144 rows, complex128,
-// 14 x 14 20.1 us with 1024 blocks and 15.1 with 256, 40 x 40 91 us with 256 and 75
-// with 512; 4096000 rows, complex64, 16 x 16 118 us with 1024 blocks and 141 with
-// 256; 20000 rows, 10 x 10 9.9 us with 256 blocks, 7.5 with 156.
-inline int64_t gram_row_blocks(int64_t n, bool wide) {
-    return std::max({std::min<int64_t>(128, n / 32), std::min<int64_t>(256, n / 128),
-                     std::min<int64_t>(wide ? 512 : 1024, n / (wide ? 512 : 1024)), (int64_t)1});
+// rows, and from some row count on two per CU.  Nothing in between: with 273 blocks
+// (140000 rows) 17 CUs did two and the call took as long as with 512 (us, 256 / 273 /
+// 512 blocks: complex128, 64 x 64 116 / 149 / 100, 56 x 48 63 / 102 / 73, 24 x 24
+// 25 / 31 / 28).  The partials cost 2 KiB per tile and block, written and read.
+//   One per CU reads best where the operands are the bound and a block has enough of
+// them in flight: complex128 up to 8 tiles (1200000 rows, 256 / 512 / 1024: 16 x 16
+// 108 / 111 / 120, 48 x 8 185 / 186 / 198; 3000000 rows, 32 x 16 384 / 391 / 399).
+// complex64 has half the bytes in flight: 3000000 rows, 16 x 16 147 / 142 / 150,
+// 32 x 16 272 / 241 / 236, but 800000 rows 38 / 40 / 46 and 79 / 73 / 76.
+//   Two per CU (two waves per SIMD) where the matrix unit is: from 262144 rows
+// (complex128, 40 x 24 55 / 51, 64 x 64 198 / 165), with more than 21 tiles of
+// complex128 from half of that (180000 rows, 40 x 40 53 / 49, 64 x 64 143 / 119;
+// complex64 64 x 64 102 / 107).
+inline int64_t gram_row_blocks(int64_t n, int tiles, bool c64) {
+    const int64_t two = tiles > 8 ? (tiles > 21 && !c64 ? 1 << 17 : 1 << 18) : c64 ? 1 << 20 : INT64_MAX;
+    return n >= two ? 512 : std::max({std::min<int64_t>(128, n / 32), std::min<int64_t>(256, n / 128), (int64_t)1});
 }
 
 // Scratch (complex128 entries) at which no n-row Gram of these widths runs with
-// fewer row blocks than it wants, whatever its tile list (X and Y apart, or Y
-// among X's columns, whose two ranges may take one unit more).
+// fewer row blocks than it wants, whatever its type and tile list (X and Y apart, or Y
+// among X's columns, whose two ranges may take one unit more): more tiles want no
+// fewer blocks.
 inline size_t gram_part_entries(int64_t n, int bx, int by) {
     if (n <= 1024) return 0;
-    const size_t tiles = (size_t)(gram_units(bx) + 1) * gram_units(by);
-    return 128 * std::max(tiles * gram_row_blocks(n, true), std::min<size_t>(tiles, 8) * gram_row_blocks(n, false));
+    const int tiles = (gram_units(bx) + 1) * gram_units(by);
+    return (size_t)128 * tiles * std::max(gram_row_blocks(n, tiles, false), gram_row_blocks(n, tiles, true));
 }
 
 }  // namespace gplhr

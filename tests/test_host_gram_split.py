@@ -21,7 +21,7 @@ def split(tmp_path_factory):
         if k == "s":
             scratch[v[0], v[1], v[2]] = v[3]
         else:
-            blocks[v[0], v[1]] = (v[2], v[3])
+            blocks[v[0], v[1], v[2]] = (v[3], v[4])
     return scratch, blocks
 
 
@@ -41,13 +41,14 @@ def test_scratch_holds_the_wanted_row_blocks(split):
     scratch, blocks = split
     for (n, bx, by), have in scratch.items():
         for tiles, rule in _tiles(bx, by):
-            few, want = blocks[n, rule]
-            assert few or have >= 128 * tiles * want, (n, bx, by, tiles)
+            for c64 in (0, 1):
+                few, want = blocks[n, rule, c64]
+                assert few or have >= 128 * tiles * want, (n, bx, by, tiles)
 
 
 def test_scratch_of_a_projection_follows_its_rows(split):
     # a tile's partial is 128 entries; one row block per 128 rows, but 128 of them
-    # from 4096 rows on and no more than 512 (8 tiles or fewer: 1024)
+    # from 4096 rows on and no more than 512
     scratch, _ = split
     for (n, wg, w), have in scratch.items():
         if w > 48 or wg < w or wg - w > 48:
@@ -56,4 +57,13 @@ def test_scratch_of_a_projection_follows_its_rows(split):
         if n <= 1024:
             assert have == 0
         assert have <= 128 * tiles * max(128, n // 128), (n, wg, w)
-        assert have <= 128 * max(512 * tiles, 8 * 1024), (n, wg, w)
+        assert have <= 128 * 512 * tiles, (n, wg, w)
+
+
+def test_row_blocks_fill_the_cus_evenly(split):
+    # beyond one block per CU (256) each CU takes the same number, or the CUs with
+    # one more set the time; all rows are covered, by at least 32 per block
+    _, blocks = split
+    for (n, tiles, c64), (_, nblk) in blocks.items():
+        assert 1 <= nblk <= 256 or nblk % 256 == 0, (n, tiles, c64, nblk)
+        assert nblk == 1 or n // nblk >= 32

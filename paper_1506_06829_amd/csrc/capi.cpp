@@ -472,8 +472,7 @@ gplhr_status gplhr_proj_orth(int dtype, int64_t n, void *Z, int ld, int wy, int 
 // process ends.  In host code `scratch` names a host-side stand-in, so kernels
 // get the device address that hipGetSymbolAddress returns for the current
 // device (kept per device below), never the array's name.
-static constexpr size_t NOALLOC_SCRATCH_ENTRIES = (size_t)1 << 20;   // complex128, 16 MiB
-static __device__ __align__(256) double2 scratch[NOALLOC_SCRATCH_ENTRIES];
+static __device__ __align__(256) double2 scratch[gplhr::GRAM_NOALLOC_ENTRIES];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -522,18 +521,16 @@ gplhr_status gplhr_gram_noalloc(int dtype, int64_t n, const void *X, int ldx, in
         if (n < 1 || bx < 1 || by < 1 || bx > 64 || by > 64 || ldx < bx || ldy < by ||
             (dtype != 0 && dtype != 1) || !X || !Y || !G)
             throw gplhr::Error(-1, "gplhr_gram_noalloc: bad arguments");
-        // one block's partial Gram takes 128 entries per 16x16 tile, at most 64
-        // tiles: the kernel uses as many blocks as fit
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
         double2 *part = scratch_on_current_device();
         if (dtype == 0)
             gplhr::launch_gram<double2>(st, n, static_cast<const double2 *>(X), ldx, bx,
                                         static_cast<const double2 *>(Y), ldy, by, nullptr, part,
-                                        NOALLOC_SCRATCH_ENTRIES, static_cast<double2 *>(G), bx);
+                                        gplhr::GRAM_NOALLOC_ENTRIES, static_cast<double2 *>(G), bx);
         else
             gplhr::launch_gram<float2>(st, n, static_cast<const float2 *>(X), ldx, bx,
                                        static_cast<const float2 *>(Y), ldy, by, nullptr, part,
-                                       NOALLOC_SCRATCH_ENTRIES, static_cast<double2 *>(G), bx);
+                                       gplhr::GRAM_NOALLOC_ENTRIES, static_cast<double2 *>(G), bx);
         return 0;
     });
 }

@@ -43,4 +43,9 @@ inline size_t gram_part_entries(int64_t n, int bx, int by) {
     return (size_t)128 * tiles * std::max(gram_row_blocks(n, tiles, false), gram_row_blocks(n, tiles, true));
 }
 
+// Scratch of gplhr_gram_noalloc, kept on each GPU (64 MiB): X and Y apart always run
+// with the row blocks they want, as in gplhr_gram.  With 16 MiB, 63 x 61 complex128
+// had 128 blocks of 512 (1200000 rows: 1661 us, 686 with them all).
+constexpr size_t GRAM_NOALLOC_ENTRIES = (size_t)4 << 20;
+
 }  // namespace gplhr

@@ -1,6 +1,6 @@
 // For every pair of widths and a range of row counts, one line:
 // n bx by scratch-entries; then for every tile count and type (1 complex64)
-// "t n tiles type few blocks".
+// "t n tiles type few blocks"; last "c entries" of the call that allocates nothing.
 #include <cstdio>
 
 #include "gram_split.h"
@@ -17,5 +17,6 @@ int main() {
                 std::printf("t %lld %d %d %d %lld\n", (long long)n, t, c64, (int)gplhr::gram_few_rows(n, t),
                             (long long)gplhr::gram_row_blocks(n, t, c64));
     }
+    std::printf("c %zu\n", gplhr::GRAM_NOALLOC_ENTRIES);
     return 0;
 }

@@ -10,19 +10,17 @@ ROOT = Path(__file__).resolve().parents[1]
 
 
 @pytest.fixture(scope="module")
-def split(tmp_path_factory):
+def lines(tmp_path_factory):
     exe = tmp_path_factory.mktemp("split") / "harness"
     subprocess.run(["g++", "-O1", "-std=c++17", f"-I{ROOT / 'paper_1506_06829_amd' / 'csrc'}",
                     str(ROOT / "tests" / "host_gram_split_harness.cpp"), "-o", str(exe)], check=True)
-    scratch, blocks = {}, {}
-    for l in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines():
-        k, *v = l.split()
-        v = list(map(int, v))
-        if k == "s":
-            scratch[v[0], v[1], v[2]] = v[3]
-        else:
-            blocks[v[0], v[1], v[2]] = (v[3], v[4])
-    return scratch, blocks
+    out = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout
+    return [(l[0], tuple(map(int, l[1:].split()))) for l in out.splitlines()]
+
+
+@pytest.fixture(scope="module")
+def split(lines):
+    return ({v[:3]: v[3] for k, v in lines if k == "s"}, {v[:3]: v[3:] for k, v in lines if k == "t"})
 
 
 def _tiles(bx, by):
@@ -67,3 +65,11 @@ def test_row_blocks_fill_the_cus_evenly(split):
     for (n, tiles, c64), (_, nblk) in blocks.items():
         assert 1 <= nblk <= 256 or nblk % 256 == 0, (n, tiles, c64, nblk)
         assert nblk == 1 or n // nblk >= 32
+
+
+def test_kept_scratch_never_costs_row_blocks(split, lines):
+    # gplhr_gram_noalloc of two blocks runs with the row blocks of gplhr_gram
+    _, blocks = split
+    kept, = [v[0] for k, v in lines if k == "c"]
+    for (n, tiles, c64), (few, want) in blocks.items():
+        assert few or tiles > 64 or kept >= 128 * tiles * want, (n, tiles, c64)

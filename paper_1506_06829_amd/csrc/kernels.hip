@@ -405,8 +405,9 @@ static void launch_update_mfma(hipStream_t st, const UpdArgs<T> &a, int kpad) {
 // when Out is overwritten, complex128 pointers aligned to their 16-byte entries,
 // row strides within the kernel's 32-bit offsets.
 template <typename T>
-static bool update_stream(hipStream_t st, UpdArgs<T> a, int kpad) {
-    if (a.nterms < 1 || kpad < 8 || kpad > 64 || a.add) return false;
+static bool update_stream(hipStream_t st, const UpdArgs<T> &all, int kpad) {
+    if (all.nterms < 1 || kpad < 8 || kpad > 64 || all.add) return false;
+    UpdStreamArgs<T> a{all};
     auto al16 = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
     auto far = [](int64_t ld) { return (16 * ld + 64) * (int64_t)sizeof(T) > (int64_t)UINT32_MAX; };
     if (far(a.ldo) || a.n > ((int64_t)UINT32_MAX - 65536) * 16) return false;

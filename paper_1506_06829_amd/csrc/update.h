@@ -46,7 +46,14 @@ struct UpdArgs {
     int wtot;
     const T *add;    // added block (column c at add[c]) or null
     int ldadd;
-    // update_stream_kernel: the slabs of 8 input columns of all terms in order
+};
+
+// With what update_stream_kernel takes besides: a struct of its own, as a launch's
+// argument bytes cost time (these 224 took 0.25 us of update_mfma_kernel's 5 on small
+// blocks).
+template <typename T>
+struct UpdStreamArgs : UpdArgs<T> {
+    // the slabs of 8 input columns of all terms in order
     struct Slab {
         const void *p;   // row 0, the slab's first column
         int64_t ldb;     // bytes of a row
@@ -98,7 +105,7 @@ __host__ __device__ __forceinline__ int pad8(int w) { return (w + 7) & ~7; }
 // nts (pieces never do: update_stream).
 template <typename T, int NT, int SL, bool BETA, bool TRI, bool RAG, bool SCL, bool VEC, bool RUN = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8)))
-void update_stream_kernel(UpdArgs<T> a, int nslab, int nts) {
+void update_stream_kernel(UpdStreamArgs<T> a, int nslab, int nts) {
     using M = UpdMma<T>;
     using R = typename M::R;
     using V = typename M::V;
@@ -400,7 +407,7 @@ void update_stream_kernel(UpdArgs<T> a, int nslab, int nts) {
     }
 }
 
-template <typename T> using UpdFn = void (*)(UpdArgs<T>, int, int);
+template <typename T> using UpdFn = void (*)(UpdStreamArgs<T>, int, int);
 struct UpdKind {
     bool beta, tri, rag, scl, vec, run;
 };

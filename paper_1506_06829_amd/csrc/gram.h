@@ -40,7 +40,7 @@
 // complex128 2450 -> 2290; X^H X of 48 columns 1366 -> 655 / 1350 -> 876;
 // [Y X]^H X of 16 + 48 columns 1810 -> 1035 / 1816 -> 1215, of 48 + 16 complex128
 // 590 -> 531 (5.9 TB/s); 262144 rows, complex128, 40 x 40 95 -> 75, 56 x 56
-// 219 -> 150; 1024 rows, 32 x 32 20.6 -> 8.7.
+// 219 -> 150.
 #pragma once
 #include "device_math.h"
 
@@ -90,11 +90,14 @@ constexpr int gram_groups(int ma, int mb, int a1, bool tri) {
 // Four groups of a rectangular product: quadrants (of an odd unit count, halves
 // that share the middle unit), which read fewer units than ranges of the list
 // and share one body, so that the registers of several bodies don't add up.
-// Ranges stay where they fit without spilling and share less work (2000000 rows,
-// us as ranges / as quadrants): complex128, 56 x 56 1043 / 1086; complex64, 56 x 40
-// 706 / 806, scaled 56 x 56 1007 / 1090.  Elsewhere quadrants: complex128, 56 x 40
-// 1322 / 835, 64 x 40 1050 / 845, 64 x 56 2565 / 1145, scaled 56 x 56 2313 / 1170;
-// complex64, 64 x 56 2069 / 985, 56 x 56 1166 / 982.
+// Ranges stay where they are the faster ones, as their groups share less work
+// (2000000 rows, us as ranges / as quadrants): complex128, 56 x 56 1043 / 1086;
+// complex64, 56 x 40 706 / 806, scaled 56 x 56 1007 / 1090; 262144 rows, 56 x 48
+// 106 / 112 (1200000 471 / 481, 4000000 1699 / 1688).  These spill a little at the
+// limit of 256 registers (28 to 52 bytes a lane; 56 x 40 does not), as does X^H X of
+// 48 with 24 more columns (complex128, 16 bytes).  Elsewhere quadrants: complex128,
+// 56 x 40 1322 / 835, 64 x 40 1050 / 845, 64 x 56 2565 / 1145, scaled 56 x 56
+// 2313 / 1170; complex64, 64 x 56 2069 / 985, 56 x 56 1166 / 982.
 template <typename T>
 constexpr bool gram_quads(int ma, int mb, bool tri, bool scaled) {
     if (tri || gram_groups(ma * mb) != 4) return false;
@@ -130,7 +133,9 @@ constexpr GramPlan gram_plan(int g) {
 }
 
 // K steps in flight per wave: about 48 registers of operands, fewer beside
-// many accumulators.
+// many accumulators.  complex64 with 13 or 14 tiles would spill with four (us, four /
+// three: 1200000 rows, 56 x 16 155 / 145, 56 x 32 289 / 267, scaled 40 x 40 277 / 269;
+// 262144 rows 44.2 / 42.8, 70.2 / 67.8, 66.7 / 66.5).
 template <typename T, int MA, int MB, int A1, bool TRI, int SC0>
 constexpr int gram_pf() {
     constexpr int NT = gram_tiles(MA, MB, A1, TRI), G = gram_groups(MA, MB, A1, TRI);
@@ -144,6 +149,7 @@ constexpr int gram_pf() {
     }
     const int regs = most * (int)sizeof(T) / 8 + (SC0 < MB ? (int)sizeof(T) / 4 : 0);
     const int pf = (tiles > 12 ? G == 4 && !gram_quads<T>(MA, MB, TRI, SC0 < MB) ? 30 : 40 : 56) / regs;
+    if (sizeof(T) == 8 && (tiles == 13 || tiles == 14) && pf == 4) return 3;
     return pf < 2 ? 2 : pf > 8 ? 8 : pf;
 }
 

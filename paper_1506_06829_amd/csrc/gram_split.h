@@ -13,12 +13,14 @@ constexpr int gram_units(int w) { return (w + 7) / 8; }
 // per tile takes all rows (gram_tile_kernel) and there are no partials.
 inline bool gram_few_rows(int64_t n, int tiles) { return n <= 1024 || (n <= 2048 && tiles > 16); }
 
-// Row blocks of the kernels with partials: one per 32 rows while that leaves CUs idle
-// (a wave then has two K steps, both in flight at once), up to one per CU at 128
-// rows, and from some row count on two per CU.  Nothing in between: with 273 blocks
-// (140000 rows) 17 CUs did two and the call took as long as with 512 (us, 256 / 273 /
-// 512 blocks: complex128, 64 x 64 116 / 149 / 100, 56 x 48 63 / 102 / 73, 24 x 24
-// 25 / 31 / 28).  The partials cost 2 KiB per tile and block, written and read.
+// Row blocks of the kernels with partials: one per 32 rows while that leaves half of the
+// CUs idle (us at 16 / 32 / 64 / 128 rows: 3000 rows, complex128, 10 x 10 7.5 / 7.1 / 7.2 /
+// 7.4, 64 x 64 18.1 / 15.6 / 17.9 / 24.2; 8192 rows 11.2 / 8.2 / 7.4 / 7.8 and 28 / 22 /
+// 20 / 26, with 128 blocks of 64), up to one per CU at 128 rows (20000 rows, 10 x 10
+// 14.4 / 14.4 / 10.5 / 8.3), and from some row count on two per CU.  Nothing in between:
+// with 273 blocks (140000 rows) 17 CUs had two, for longer than all with two take (us,
+// 256 / 273 / 512 blocks: complex128, 64 x 64 116 / 149 / 100, 56 x 48 63 / 102 / 73,
+// 24 x 24 25 / 31 / 28).  The partials cost 2 KiB per tile and block, written and read.
 //   One per CU reads best where the operands are the bound and a block has enough of
 // them in flight: complex128 up to 8 tiles (1200000 rows, 256 / 512 / 1024: 16 x 16
 // 108 / 111 / 120, 48 x 8 185 / 186 / 198; 3000000 rows, 32 x 16 384 / 391 / 399).

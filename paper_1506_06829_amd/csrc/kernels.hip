@@ -91,7 +91,8 @@ void launch_reduce_partials(hipStream_t st, const double2 *part, int nblk, int b
 // Out = beta Out + Add + sum_t alpha_t diag(rs_t) In_t M_t, row by row.
 // update_stream_kernel (update.h) takes up to 64 input columns.  The two kernels
 // here compute the rest: an MFMA kernel for wider inputs, a row scale together
-// with beta != 0, and blocks it cannot address; and a VALU kernel that gives
+// with beta != 0, blocks it cannot address, and unaligned complex64 entries from
+// few columns to many; and a VALU kernel that gives
 // each lane one row, for a plain copy of Add, for narrow complex64 outputs of
 // wide inputs and for coefficients the MFMA kernel cannot stage.  All read the
 // inputs of a row before they write its outputs, so Out may alias any input.
@@ -470,8 +471,8 @@ static bool update_stream(hipStream_t st, const UpdArgs<T> &all, int kpad) {
     const bool one = gaps && (sizeof(T) == 16 ? ns >= 3 || (ns == 2 && k.rag) : ns >= 3 && ns <= 6);
     const bool few = gaps && nt >= 2 * ns && (sizeof(T) == 8 ? ns <= 2 : ns == 1 && ((a.ldo | a.wout) & 3) != 0);
     const int run_waves = few ? 2 : one || coef + 4 * tile <= lds / 2 ? 4 : 8;
-    k.run = big && (lines ? nt >= 2 * ns : gaps || nt >= ns) && ns * nt <= 40 && coef + run_waves * tile <= lds &&
-            (int64_t)rows * a.ldo * (int64_t)sizeof(T) <= (int64_t)UINT32_MAX;
+    k.run = big && (lines ? nt >= 2 * ns : gaps || nt >= ns) && ns * nt <= UPD_RUN_TILES &&
+            coef + run_waves * tile <= lds && (int64_t)rows * a.ldo * (int64_t)sizeof(T) <= (int64_t)UINT32_MAX;
     const UpdFn<T> fn = update_pick<T>(nt, ns, k);
     if (!fn) return false;
     // Two waves per SIMD, persistent: more only spread the accesses (4096000
@@ -490,13 +491,15 @@ static bool update_stream(hipStream_t st, const UpdArgs<T> &all, int kpad) {
     return true;
 }
 
-// MFMA or VALU kernel, by measurement at 4096000 and 262144 rows: in FP64 the
-// MFMA kernel is as fast or faster for every shape;
-// for complex64 it wins once the output is wider than 16 columns, Out is
-// accumulated into, or the output fills its 8- or 16-column tiles (16 -> 16
-// overwrite at 262144 rows: 25.8 -> 19.2 us, 48 -> 16: 50.4 -> 39.4 us); the
-// VALU kernel's coalesced row segments win for narrow overwrites that would
-// leave tile columns empty (10 -> 10 at 4096000 rows: 200 against 239 us).
+// MFMA or VALU kernel for what update_stream leaves (us, MFMA / VALU): complex64 takes the
+// MFMA kernel once the output is wider than 16 columns, Out is accumulated into, or the
+// output fills its 8- or 16-column tiles (4096000 rows, 72 -> 16 768 / 856, 96 -> 24 1642 /
+// 2240; 262144 rows, 72 -> 8 40 / 49, 72 -> 10 accumulated 54 / 63); the VALU kernel's
+// coalesced row segments win for narrow overwrites that would leave tile columns empty
+// (4096000 rows, 72 -> 10 757 / 669, 128 -> 10 1379 / 1114; 262144 rows 50 / 54, 96 / 86).
+// In FP64 always the MFMA kernel (4096000 rows, 72 -> 16 1473 / 1933, 72 -> 32 2152 / 5138;
+// 262144 rows, 96 -> 10 133 / 140), also for the fewest columns, where the VALU kernel is
+// the faster one (4096000 rows, 72 -> 4 1273 / 969, 72 -> 10 1446 / 1267).
 template <typename T>
 static bool update_mfma(const UpdArgs<T> &a, int kpad, hipStream_t st) {
     if (a.nterms < 1 || kpad < 8) return false;

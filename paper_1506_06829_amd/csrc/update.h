@@ -411,7 +411,11 @@ template <typename T> using UpdFn = void (*)(UpdStreamArgs<T>, int, int);
 struct UpdKind {
     bool beta, tri, rag, scl, vec, run;
 };
-// The kernel for nt output tiles and sl slabs, or null.
+// Most coefficient tiles (slabs by output tiles) of a run kernel.
+constexpr int UPD_RUN_TILES = 40;
+// The kernel for nt output tiles and sl slabs, or null.  At the limit of 256 registers
+// three complex128 ones spill 12 to 36 bytes a lane: 8 slabs by 5 and by 6 tiles
+// accumulated into Out, 8 by 6 row-scaled.
 template <typename T> UpdFn<T> update_pick(int nt, int sl, UpdKind k);
 
 template <typename T, int NT, int SL>
@@ -427,9 +431,12 @@ UpdFn<T> update_pick_shape(UpdKind k) {
     if (k.scl) return k.beta ? nullptr : update_stream_kernel<T, NT, SL, false, false, true, true, true>;
     if (k.beta) return update_stream_kernel<T, NT, SL, true, false, true, false, true>;
     if (k.run) {
-        if constexpr (NT >= 2 && NT <= SL)
-            if (k.tri) return update_stream_kernel<T, NT, SL, false, true, true, false, true, true>;
-        return update_stream_kernel<T, NT, SL, false, false, true, false, true, true>;
+        if constexpr (NT * (SL - 1) > UPD_RUN_TILES) return nullptr;   // SL - 1 slabs or SL
+        else {
+            if constexpr (NT >= 2 && NT <= SL)
+                if (k.tri) return update_stream_kernel<T, NT, SL, false, true, true, false, true, true>;
+            return update_stream_kernel<T, NT, SL, false, false, true, false, true, true>;
+        }
     }
     if constexpr (NT >= 2 && NT <= SL)
         if (k.tri)

@@ -127,7 +127,10 @@ constexpr int spmm_unstaged() {
     return BATCH == 12 ? 10 : BATCH == 17 && MODE == 3 ? 12 : BATCH;
 }
 
-template <typename T, int CPL, int MODE, int BATCH, bool S32>
+// CHECK: the kernel asks the row pointers for the order of the rows; a kernel of its
+// own, as a plane schedule lost 5 % to these lines without taking them (160^3 operator,
+// 16 complex128 columns 636 us, 666 with them).
+template <typename T, int CPL, int MODE, int BATCH, bool S32, bool CHECK>
 __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
     constexpr int WS = SPMM_STAGE<T>;
     __shared__ uint32_t s_ci[4 * WS];   // S32: byte offset of the block row
@@ -145,19 +148,19 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
     const auto mine = [&](SpmmRows r) {
         return SpmmRows{r.row0 + wv * a.s.rpw, min(a.s.rpw, r.nr - wv * a.s.rpw)};
     };
-    const bool check = a.s.order == SPMM_CHECK;
     int ends = 0;   // lanes 0 .. 8: the row pointers at the eighths' ends
-    if (check) ends = a.rp[min(min(lane, 8) * ((uint32_t)a.s.nbs * (uint32_t)a.s.rpb), (uint32_t)a.n)];
+    if constexpr (CHECK) ends = a.rp[min(min(lane, 8) * ((uint32_t)a.s.nbs * (uint32_t)a.s.rpb), (uint32_t)a.n)];
     SpmmRows rows = mine(a.s.sp > 0 ? spmm_plane_rows(a.s, blockIdx.x)
                                     : spmm_natural_rows(a.s, a.n, blockIdx.x, a.s.order != SPMM_TURN));
     const auto entries = [&](const SpmmRows &r, int &first, int &count) {
-        const int64_t r0 = min(r.row0, a.n);
+        const int64_t r0 = CHECK ? min(r.row0, a.n) : r.row0;   // (CHECK: also waves without rows)
         first = __builtin_amdgcn_readfirstlane(a.rp[r0]);
-        count = __builtin_amdgcn_readfirstlane(a.rp[r0 + max(r.nr, 0)]) - first;
+        count = __builtin_amdgcn_readfirstlane(a.rp[r0 + (CHECK ? max(r.nr, 0) : r.nr)]) - first;
     };
+    if (!CHECK && rows.nr <= 0) return;
     int e0, ne;
     entries(rows, e0, ne);
-    if (check) {
+    if constexpr (CHECK) {
         const int more = __builtin_amdgcn_update_dpp(0, ends, 0x101, 0xf, 0xf, false) - ends;   // entries of eighth `lane`
         const int total = __builtin_amdgcn_readlane(ends, 8) - __builtin_amdgcn_readfirstlane(ends);
         if (__ballot(lane < 8 && !spmm_even(more, total))) {
@@ -165,7 +168,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(SpmmArgs<T> a) {
             entries(rows, e0, ne);
         }
     }
-    if (rows.nr <= 0) return;
+    if (CHECK && rows.nr <= 0) return;
     const int64_t row0 = rows.row0;
     const int nr = rows.nr;
     uint32_t *w_ci = s_ci + wv * WS;
@@ -322,8 +325,12 @@ template <typename T, int MODE, int BATCH>
 static void spmm_go(hipStream_t st, const SpmmArgs<T> &a, int cpl, int grid) {
     // block rows and columns within 32-bit byte offsets
     const bool s32 = (double)a.n * a.ldx * sizeof(T) + (double)a.b * sizeof(T) < 4294967296.0;
-    const auto fn = cpl == 2 ? (s32 ? spmm_kernel<T, 2, MODE, BATCH, true> : spmm_kernel<T, 2, MODE, BATCH, false>)
-                             : (s32 ? spmm_kernel<T, 1, MODE, BATCH, true> : spmm_kernel<T, 1, MODE, BATCH, false>);
+    const auto pick = [&](auto check) {
+        constexpr bool C = decltype(check)::value;
+        return cpl == 2 ? (s32 ? spmm_kernel<T, 2, MODE, BATCH, true, C> : spmm_kernel<T, 2, MODE, BATCH, false, C>)
+                        : (s32 ? spmm_kernel<T, 1, MODE, BATCH, true, C> : spmm_kernel<T, 1, MODE, BATCH, false, C>);
+    };
+    const auto fn = a.s.order == SPMM_CHECK ? pick(std::true_type{}) : pick(std::false_type{});
     hipLaunchKernelGGL(fn, dim3(grid), dim3(256), 0, st, a);
 }
 

@@ -167,7 +167,7 @@ static void launch_gram_impl(hipStream_t st, int64_t n, const T *X, int ldx, int
         return;
     }
     const int ks = 4 / gram_groups(a.ma, a.mb, a.ma1, a.tri);
-    int64_t nblk = gram_row_blocks(n, tiles, sizeof(T) == 8);
+    int64_t nblk = gram_row_blocks(n, tiles, sizeof(T) == 8, Y2 != nullptr);
     nblk = std::min<int64_t>(nblk, (int64_t)(part_cap / (128 * (size_t)a.ntile)));
     if (nblk < 1) throw Error(-1, "gram: partial buffer too small");
     a.rows_per_blk = ((n + nblk - 1) / nblk + 4 * ks - 1) / (4 * ks) * (4 * ks);

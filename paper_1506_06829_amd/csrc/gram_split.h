@@ -25,13 +25,17 @@ inline bool gram_few_rows(int64_t n, int tiles) { return n <= 1024 || (n <= 2048
 // them in flight: complex128 up to 8 tiles (1200000 rows, 256 / 512 / 1024: 16 x 16
 // 108 / 111 / 120, 48 x 8 185 / 186 / 198; 3000000 rows, 32 x 16 384 / 391 / 399).
 // complex64 has half the bytes in flight: 3000000 rows, 16 x 16 147 / 142 / 150,
-// 32 x 16 272 / 241 / 236, but 800000 rows 38 / 40 / 46 and 79 / 73 / 76.
+// 32 x 16 272 / 241 / 236, but 800000 rows 38 / 40 / 46 and 79 / 73 / 76.  So has
+// complex128 with a second Y (and scale) to 16 columns (4000000 rows, [16 16] scaled
+// 569 / 519 / 531, [10 10] 393 / 362 / 370, not scaled 496 / 506 / 520).
 //   Two per CU (two waves per SIMD) where the matrix unit is: from 262144 rows
 // (complex128, 40 x 24 55 / 51, 64 x 64 198 / 165), with more than 21 tiles of
 // complex128 from half of that (180000 rows, 40 x 40 53 / 49, 64 x 64 143 / 119;
 // complex64 64 x 64 102 / 107).
-inline int64_t gram_row_blocks(int64_t n, int tiles, bool c64) {
-    const int64_t two = tiles > 8 ? (tiles > 21 && !c64 ? 1 << 17 : 1 << 18) : c64 ? 1 << 20 : INT64_MAX;
+inline int64_t gram_row_blocks(int64_t n, int tiles, bool c64, bool pair = false) {
+    const int64_t two = tiles > 8                     ? (tiles > 21 && !c64 ? 1 << 17 : 1 << 18)
+                        : c64 || (pair && tiles == 8) ? 1 << 20
+                                                      : INT64_MAX;
     return n >= two ? 512 : std::max({std::min<int64_t>(128, n / 32), std::min<int64_t>(256, n / 128), (int64_t)1});
 }
 

@@ -19,15 +19,14 @@
 // stored; rows past the end are a masked step of their own after the loop).
 //
 // The four waves of a workgroup form G tile groups times KS = 4 / G row
-// splits.  G = 1 up to 21 tiles, 2 up to 34, else 4 (at most 168 accumulator
+// splits.  G = 1 up to 21 tiles (TRI: 17), 2 up to 34, else 4 (at most 168 accumulator
 // registers, two waves per SIMD); each group is a range of the tile list with
 // a body of its own, so that the groups differ by one tile at most.  The waves of one row
 // split read the same rows at about the same time, from L1.  A range of a few whole
 // columns of the list reads all of A again, so one group is the better while its
 // accumulators fit (1200000 rows, us, two groups / one): complex128 47 x 21 326 / 229,
-// 40 x 32 308 / 247, 56 x 24 401 / 269, X's last 24 of 64 columns 371 / 229; complex64
-// 48 x 24 197 / 186, 40 x 32 210 / 200.  24 tiles in one group spill (complex64 48 x 32
-// 250 / 264).
+// 40 x 32 308 / 247, 56 x 24 401 / 269; complex64 48 x 24 197 / 186, 40 x 32 210 / 200.
+// 24 tiles in one group spill (complex64 48 x 32 250 / 264).
 //
 // TRI: Y is X's last `w` columns (X^H X of a Cholesky-QR step, [Y X]^H X of a
 // projection): operands are loaded once, and of the Hermitian part only the
@@ -81,11 +80,11 @@ constexpr int gram_tiles(int ma, int mb, int a1, bool tri) {
 }
 // Most tiles of a wave (of a kernel with one tile group; two have 17, four 16).
 constexpr int GRAM_MAX_TILES = 21;
-constexpr int gram_groups(int tiles) { return tiles <= GRAM_MAX_TILES ? 1 : tiles <= 34 ? 2 : 4; }
+constexpr int gram_groups(int tiles, bool tri) { return tiles <= (tri ? 17 : GRAM_MAX_TILES) ? 1 : tiles <= 34 ? 2 : 4; }
 // Tile groups of a kernel.  X^H X of up to 5 units splits its rows as X^H Y of
 // those widths does, so that the same block passed as a copy gives the same bits.
 constexpr int gram_groups(int ma, int mb, int a1, bool tri) {
-    return gram_groups(tri && a1 == 0 && ma <= 5 ? ma * mb : gram_tiles(ma, mb, a1, tri));
+    return tri && a1 == 0 && ma <= 5 ? gram_groups(ma * mb, false) : gram_groups(gram_tiles(ma, mb, a1, tri), tri);
 }
 // Four groups of a rectangular product: quadrants (of an odd unit count, halves
 // that share the middle unit), which read fewer units than ranges of the list
@@ -100,7 +99,7 @@ constexpr int gram_groups(int ma, int mb, int a1, bool tri) {
 // 2313 / 1170; complex64, 64 x 56 2069 / 985, 56 x 56 1166 / 982.
 template <typename T>
 constexpr bool gram_quads(int ma, int mb, bool tri, bool scaled) {
-    if (tri || gram_groups(ma * mb) != 4) return false;
+    if (tri || gram_groups(ma * mb, false) != 4) return false;
     if (ma % 2 == 0 && mb % 2 == 0) return true;
     return sizeof(T) == 16 ? ma != mb || scaled : mb == 7 && !scaled;
 }

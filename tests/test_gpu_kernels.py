@@ -456,7 +456,7 @@ def test_gram_of_odd_unit_counts(device, bx, by, dtype):
                                        (57, 17, False), (45, 45, True), (43, 36, True), (46, 30, True), (62, 22, True)])
 @pytest.mark.parametrize("dtype", ["c128", "c64"])
 def test_gram_of_18_to_24_tiles(device, bx, by, own, dtype):
-    # up to 21 tiles one wave holds all of them, from 22 on two share them: row
+    # up to 21 tiles of two blocks one wave holds all of them, else two share them: row
     # counts around a K step, a wave's steps and a row block.  Bound as above:
     # n products per entry.
     import torch

@@ -43,14 +43,14 @@ DOMINANT_KERNEL_PROBE = "Gram c64 64x64"
 # read for a 256 MiB device copy), valid only for the kernel sources whose
 # SHA-256 prefix is recorded with it; any later change to them makes the
 # reported traffic null until the counters are taken again.
-DOMINANT_KERNEL_TRAFFIC = 4262329088          # bytes per launch
-DOMINANT_KERNEL_TRAFFIC_SRC = "bcbfc85d30952bc0"   # sha256 prefix of the Gram's sources
+DOMINANT_KERNEL_TRAFFIC = 4264077619          # bytes per launch
+DOMINANT_KERNEL_TRAFFIC_SRC = "ab40fa4e86652068"   # sha256 prefix of the Gram's sources
 
 
 def kernels_source_sha():
     import hashlib
     h = hashlib.sha256()
-    for name in ("device_math.h", "gram.h", "gram.hip", "gram_c64.hip"):
+    for name in ("device_math.h", "gram.h", "gram_split.h", "gram.hip", "gram_c64.hip"):
         with open(os.path.join(ROOT, "paper_1506_06829_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

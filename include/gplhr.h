@@ -306,13 +306,14 @@ const char *gplhr_last_error(gplhr_t h);
  * col_idx and val may be NULL only when every row is empty.  plane = 0 runs
  * the rows in natural order; plane > 0 (a divisor of n and a multiple of 8,
  * e.g. from gplhr_csr_plane) runs them plane by plane, each XCD of the GPU on
- * its own slab of every plane, for matrices whose couplings stay within
- * +-plane rows; the result is the same either way.  nnz is the number of
+ * its own slab of every plane (planes too thin for that in natural order), for
+ * matrices whose couplings stay within +-plane rows; the result is the same
+ * either way.  nnz is the number of
  * stored entries (row_ptr[n]); the kernel takes the entries of a row in
- * batches of 8, 12 or 17 by the typical row length nnz / n.  Only the speed
+ * batches of 5, 7, 12 or 17 by the typical row length nnz / n.  Only the speed
  * depends on it: any nnz >= 0 gives the same result.
  * Returns ARG for nnz < 0, b < 1 or b > 64, bad leading dimensions or a bad
- * plane. */
+ * plane; HIP where n and b need 2^32 threads or more. */
 gplhr_status gplhr_spmm(int dtype, int64_t n, int64_t nnz, const int32_t *row_ptr,
                         const int32_t *col_idx, const void *val, const void *X,
                         int ldx, void *Y, int ldy, int b, int plane, void *hip_stream);
